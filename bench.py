@@ -42,7 +42,7 @@ def kernel_hash():
     """Hash of the sources that decide the optimiser's work per launch (its
     kernels and the host code that sets its programs and tolerances)."""
     h = hashlib.sha256()
-    for name in ("kernels.hip", "abi.cpp", "tree.cpp"):
+    for name in ("kernels.hip", "partials.hpp", "optimize.hpp", "lanes.hpp", "prune.hip", "abi.cpp", "tree.cpp"):
         with open(os.path.join(ROOT, "paper_1811_11007_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
@@ -436,7 +436,7 @@ def main():
                          "peak": FP64_VALU_PEAK_TFLOPS, "unit": "TFLOP/s",
                          "frac": round(flops3r / (ms3r / 1e3) / 1e12 / FP64_VALU_PEAK_TFLOPS, 4),
                          "flops_per_call": flops3r, "bytes_per_call": by3r},
-            "note": "graph of k_pmat + k_loglik_reg + k_reduce"}
+            "note": "graph of k_pmat_lanes + k_prune + k_tile_sums"}
         if not args.no_search:
             log("threshold search, cold and warm-started ...")
             # the learned warm start in the threshold search (T = -10, radius-0

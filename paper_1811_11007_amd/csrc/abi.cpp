@@ -114,16 +114,14 @@ struct pt_plan {
     Op *d_ops = nullptr;
     TreeDev *d_trees_ll = nullptr, *d_trees_gr = nullptr, *d_trees_opt = nullptr;
     int32_t *d_tile_tree = nullptr, *d_edge_tree = nullptr, *d_order = nullptr, *d_queue = nullptr;
-    // the register-resident lnL (k_loglik_reg): its descriptors, tiles and
+    // the register-resident lnL (k_prune): its descriptors, tiles and
     // tile sums; reg_ok when every tree of the plan fits it
     bool reg_ok = false, stored_ok = true;
     int ll_stored = 0;  // pt_plan_set_loglik_path: 1 = the stored post-order pass
     TreeDev *d_trees_reg = nullptr;
     int32_t *d_tile_tree_reg = nullptr;
     double *d_part_reg = nullptr;
-    int n_tiles_reg = 0, reg_depth = 0;
-    size_t lds_reg = 0;
-    const double *ident = nullptr;  // the 4x4 identity, after the matrices
+    int n_tiles_reg = 0, reg_depth = 0, reg_taxa = 0, reg_items = 0;
     void *d_clv = nullptr;
     uint16_t *d_cnt = nullptr;
     double *d_pmat = nullptr, *d_part = nullptr, *d_scratch = nullptr;
@@ -311,6 +309,59 @@ size_t opt_pm_doubles(int precision, int E, int kp) {
 // matrices from an LDS copy, FP32 partials by scalar loads (none).
 size_t stored_lds(int precision, int E, int kp) {
     return precision == PT_FP64 ? (size_t)E * kp * 16 * 8 : 0;
+}
+
+// Whether the register-resident lnL takes trees of up to n taxa and `depth`
+// stack slots: up to kRegStack slots, and a tile of tip codes that keeps
+// within the LDS of a block at 256 patterns for two or four padded
+// categories, 512 for one and 128 for eight (beyond four slots, less by 64
+// bytes per slot and lane).  The kernel itself needs less.
+bool reg_fits(const pt_ctx *ctx, int kp, int n, int depth) {
+    const size_t waves = std::max(4, kp), pats = 128 * waves / kp;
+    const size_t stack = depth <= 4 ? 0 : (size_t)depth * 2 * 64 * waves * 32;
+    return depth <= pt::kRegStack && stack + (size_t)n * pats <= ctx->lds_per_block;
+}
+
+// The blocks' tiles, so that the tiles of a tree run on one XCD and find its
+// transition matrices in that XCD's L2 (consecutive blocks go to the XCDs in
+// turn): the trees are dealt, in the order given, to the XCD with the fewest
+// tiles so far, and block i takes the next tile of XCD i mod 8.  Returns
+// the blocks' trees, then the blocks' tile numbers within their tree.
+std::vector<int32_t> tiles_by_xcd(const std::vector<int> &order, const std::vector<TreeDev> &trees) {
+    std::vector<std::pair<int32_t, int32_t>> queue[pt::kXcds];
+    size_t total = 0;
+    for (int b : order) {
+        int x = 0;
+        for (int y = 1; y < pt::kXcds; ++y)
+            if (queue[y].size() < queue[x].size()) x = y;
+        for (int t = 0; t < trees[b].n_tiles; ++t) queue[x].push_back({b, t});
+        total += trees[b].n_tiles;
+    }
+    std::vector<int32_t> out(2 * total);
+    size_t next[pt::kXcds] = {};
+    for (size_t i = 0; i < total; ++i) {
+        size_t x = i % pt::kXcds;
+        while (next[x] == queue[x].size()) x = (x + 1) % pt::kXcds;  // some queue is not empty
+        out[i] = queue[x][next[x]].first;
+        out[total + i] = queue[x][next[x]].second;
+        ++next[x];
+    }
+    return out;
+}
+
+// Items per wave of the register-resident lnL for trees of up to n taxa with
+// `patterns` patterns in all: the most that still give every SIMD two waves
+// (an op's overheads are paid once per wave, but a batch of few patterns
+// needs the waves), in blocks that fit the LDS.  Measured at 2, 4 and 8
+// items: 48 trees of 27 taxa x 976 patterns (1464 waves at 8) 22.8, 19.1 and
+// 20.2 us; 512 trees over four alignments (16900 waves) 195, 150 and 141 us.
+int reg_items(const pt_ctx *ctx, int kp, int n, int64_t patterns) {
+    const int64_t want = 8LL * std::max(1, ctx->n_cu);
+    int items = pt::prune_max_items(kp);
+    while (items > 2 && (patterns / (pt::prune_tile_patterns(kp, items) / 4) < want ||
+                         pt::prune_lds(kp, items, n) > ctx->lds_per_block))
+        items /= 2;
+    return items;
 }
 
 // Sets the optimisation launch shape for `block` threads per block: patterns
@@ -533,16 +584,19 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
         if (cp[b].st) return fail(cp[b].st, cp[b].err);
     // the register-resident lnL needs every tree within its stack and the
     // tile's tip codes within the LDS of a block
-    const int reg_pats = pt::loglik_reg_tile_patterns(kp);
     pl->reg_ok = want_reg && B > 0;
     int reg_depth = 0, reg_n = 0;
     for (int b = 0; b < B; ++b) {
         reg_depth = std::max(reg_depth, cp[b].reg_depth);
         reg_n = std::max(reg_n, ntx[b]);
     }
-    if (reg_depth > pt::kRegStack || pt::loglik_reg_lds(kp, reg_n, reg_depth) > ctx->lds_per_block)
-        pl->reg_ok = false;
+    int64_t reg_patterns = 0;
+    for (int b = 0; b < B; ++b) reg_patterns += alns[trees->aln_index[b]]->P;
+    if (!reg_fits(ctx, kp, reg_n, reg_depth)) pl->reg_ok = false;
     pl->reg_depth = reg_depth;
+    pl->reg_taxa = reg_n;
+    pl->reg_items = reg_items(ctx, kp, reg_n, reg_patterns);
+    const int reg_pats = pt::prune_tile_patterns(kp, pl->reg_items);
     pl->stored_ok = true;
     for (int b = 0; b < B; ++b) pl->stored_ok = pl->stored_ok && cp[b].stored_ok;
     if ((kinds & PT_PLAN_LOGLIK) && !pl->reg_ok && !pl->stored_ok)
@@ -580,6 +634,7 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
             treg[b] = base;
             treg[b].n_tiles = (ad.P + reg_pats - 1) / reg_pats;
             append(c.rg, treg[b].op_first, treg[b].n_first);
+            treg[b].n_first -= pt::kRegAhead;
         }
         if (kinds & PT_PLAN_LOGLIK) append(c.ll, tll[b].op_first, tll[b].n_first);
         if (kinds & PT_PLAN_GRAD) append(c.gr, tgr[b].op_first, tgr[b].n_first);
@@ -603,11 +658,10 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
         for (int b = 0; b < B; ++b) order[b] = b;
         std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return pl->tree_E[x] > pl->tree_E[y]; });
         for (int b : order) {
-            treg[b].tile_begin = (int32_t)tile_tree_reg.size();
-            for (int x = 0; x < treg[b].n_tiles; ++x) tile_tree_reg.push_back(b);
+            treg[b].tile_begin = pl->n_tiles_reg;
+            pl->n_tiles_reg += treg[b].n_tiles;
         }
-        pl->lds_reg = pt::loglik_reg_lds(kp, reg_n, reg_depth);
-        pl->n_tiles_reg = (int)tile_tree_reg.size();
+        tile_tree_reg = tiles_by_xcd(order, treg);
     }
     if (kinds & (PT_PLAN_LOGLIK | PT_PLAN_GRAD)) {
         // Tiles of the trees with the longest programs first: the hardware
@@ -632,7 +686,7 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
     pl->alns_base_h = pl->alns_h;
 
     // arena cap
-    int64_t need = clv_off * (int64_t)store_bytes(precision) + cnt_off * 2 + (pm_off + 16) * 8 +
+    int64_t need = clv_off * (int64_t)store_bytes(precision) + cnt_off * 2 + pm_off * 8 +
                    (int64_t)ops.size() * sizeof(Op) + (int64_t)tiles * std::max(1, pl->max_E) * 24 +
                    (int64_t)NE * 16 + (int64_t)B * 4 * sizeof(TreeDev) + (int64_t)pl->n_tiles_reg * 28;
     int64_t cap = arena_cap();
@@ -658,10 +712,10 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
     if (kinds & PT_PLAN_OPTIMIZE) if ((st = up_trees(top, &pl->d_trees_opt))) return st;
     if (pl->reg_ok) {
         if ((st = up_trees(treg, &pl->d_trees_reg))) return st;
-        if ((st = dev_alloc(pl.get(), &pl->d_tile_tree_reg, sizeof(int32_t) * pl->n_tiles_reg))) return st;
-        PT_HIP(hipMemcpy(pl->d_tile_tree_reg, tile_tree_reg.data(), sizeof(int32_t) * pl->n_tiles_reg,
+        if ((st = dev_alloc(pl.get(), &pl->d_tile_tree_reg, sizeof(int32_t) * tile_tree_reg.size()))) return st;
+        PT_HIP(hipMemcpy(pl->d_tile_tree_reg, tile_tree_reg.data(), sizeof(int32_t) * tile_tree_reg.size(),
                          hipMemcpyHostToDevice));
-        if ((st = dev_alloc(pl.get(), &pl->d_part_reg, sizeof(double) * 3 * (size_t)pl->n_tiles_reg))) return st;
+        if ((st = dev_alloc(pl.get(), &pl->d_part_reg, sizeof(double) * (size_t)pl->n_tiles_reg))) return st;
     }
     if ((st = dev_alloc(pl.get(), &pl->d_edge_tree, sizeof(int32_t) * std::max<int64_t>(1, NE)))) return st;
     if (NE) PT_HIP(hipMemcpy(pl->d_edge_tree, edge_tree.data(), sizeof(int32_t) * NE, hipMemcpyHostToDevice));
@@ -683,14 +737,7 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
     }
     if ((st = dev_alloc(pl.get(), &pl->d_clv, (size_t)clv_off * store_bytes(precision)))) return st;
     if ((st = dev_alloc(pl.get(), &pl->d_cnt, (size_t)cnt_off * 2))) return st;
-    // the trees' matrices, then the 4x4 identity the register-resident pass
-    // applies to one side at the root edge
-    if ((st = dev_alloc(pl.get(), &pl->d_pmat, (size_t)(pm_off + 16) * 8))) return st;
-    {
-        const double ident[16] = {1, 0, 0, 0, 0, 1, 0, 0, 0, 0, 1, 0, 0, 0, 0, 1};
-        PT_HIP(hipMemcpy(pl->d_pmat + pm_off, ident, sizeof(ident), hipMemcpyHostToDevice));
-    }
-    pl->ident = pl->d_pmat + pm_off;
+    if ((st = dev_alloc(pl.get(), &pl->d_pmat, (size_t)pm_off * 8))) return st;
     PT_HIP(hipSetDevice(dev_prev));
 
     pl->lds_tiles = 0;
@@ -757,8 +804,8 @@ pt_status enqueue(pt_plan *pl, int kind, const double *brlen_c, double *brlen, c
         const bool g = kind == PT_PLAN_GRAD;
         const bool reg_ll = !g && pl->reg_ok && !pl->ll_stored;
         pt::BatchArgs a = batch_args(pl, g ? pl->d_trees_gr : pl->d_trees_ll, g ? std::max(1, pl->max_E) : 1);
-        if ((e = pt::launch_pmat(a, brlen_c, s)) != hipSuccess) goto bad;
         if (!reg_ll) {
+            if ((e = pt::launch_pmat(a, brlen_c, s)) != hipSuccess) goto bad;
             if ((e = pt::launch_tiles(pl->precision, pl->kp, pl->tile_pats, a, brlen_c, pl->lds_tiles, s)) != hipSuccess)
                 goto bad;
             if ((e = pt::launch_reduce(g, a, lnl, grad, hess, s)) != hipSuccess) goto bad;
@@ -770,12 +817,13 @@ pt_status enqueue(pt_plan *pl, int kind, const double *brlen_c, double *brlen, c
         if (reg_ll || (g && pl->reg_ok && pl->precision == PT_FP32)) {
             pt::BatchArgs r = batch_args(pl, pl->d_trees_reg, 1);
             r.tile_tree = pl->d_tile_tree_reg;
+            r.tile_of = pl->d_tile_tree_reg + pl->n_tiles_reg;
             r.part = pl->d_part_reg;
             r.n_tiles = pl->n_tiles_reg;
             r.reg_depth = pl->reg_depth;
-            r.ident = pl->ident;
-            if ((e = pt::launch_loglik_reg(pl->kp, r, pl->lds_reg, s)) != hipSuccess) goto bad;
-            if (lnl && (e = pt::launch_reduce(false, r, lnl, nullptr, nullptr, s)) != hipSuccess) goto bad;
+            r.reg_taxa = pl->reg_taxa;
+            if ((e = pt::launch_pmat_lanes(r, brlen_c, pl->max_E, s)) != hipSuccess) goto bad;
+            if ((e = pt::launch_prune(r, pl->reg_items, lnl, s)) != hipSuccess) goto bad;
         }
         return PT_OK;
     }
@@ -1136,15 +1184,19 @@ pt_status pt_batch_loglik_noalloc(pt_ctx *ctx, pt_aln *const *alns, int32_t n_al
     if (B == 0) return PT_OK;
     if (!ctx->noalloc) return fail(PT_EDEVICE, "no-allocation workspace unavailable: " + ctx->noalloc_err);
     const int kp = kp_of_plan(alns, trees);
-    const int reg_pats = pt::loglik_reg_tile_patterns(kp);
     // programs and descriptors on the host (host memory only)
     std::vector<Op> ops;
     std::vector<TreeDev> td(B);
     std::vector<AlnDev> ad(B);
     std::vector<int32_t> edge_tree(NE), tile_tree;
     std::vector<int> tree_E(B);
-    int depth = 0, n_max = 0;
-    int64_t pm_off = 0;
+    int depth = 0, n_max = 0, max_E = 0;
+    int64_t pm_off = 0, patterns = 0;
+    for (int b = 0; b < B; ++b) {
+        n_max = std::max(n_max, ntx[b]);
+        patterns += alns[trees->aln_index[b]]->P;
+    }
+    const int items = reg_items(ctx, kp, n_max, patterns), reg_pats = pt::prune_tile_patterns(kp, items);
     for (int b = 0; b < B; ++b) {
         pt::Tree t;
         std::string err;
@@ -1158,18 +1210,17 @@ pt_status pt_batch_loglik_noalloc(pt_ctx *ctx, pt_aln *const *alns, int32_t n_al
         d.pm_off = pm_off;
         d.op_first = (int32_t)ops.size();
         depth = std::max(depth, pt::compile_loglik_reg(t, ops));
-        d.n_first = (int32_t)ops.size() - d.op_first;
+        d.n_first = (int32_t)ops.size() - d.op_first - pt::kRegAhead;
         d.n_tiles = (a.P + reg_pats - 1) / reg_pats;
         td[b] = d;
         ad[b] = a;
         tree_E[b] = t.n_edges;
-        n_max = std::max(n_max, ntx[b]);
+        max_E = std::max(max_E, t.n_edges);
         pm_off += (int64_t)t.n_edges * kp * 16;
         for (int e = 0; e < t.n_edges; ++e) edge_tree[d.edge_off + e] = b;
     }
     if (depth > pt::kRegStack) return fail(PT_EUNSUPPORTED, "a tree needs more than 8 stack slots");
-    const size_t lds = pt::loglik_reg_lds(kp, n_max, depth);
-    if (lds > ctx->lds_per_block) return fail(PT_EUNSUPPORTED, "a tree exceeds the LDS of a block");
+    if (!reg_fits(ctx, kp, n_max, depth)) return fail(PT_EUNSUPPORTED, "a tree exceeds the LDS of a block");
     {   // tiles of the trees with the most edges first
         std::vector<int> order(B);
         std::iota(order.begin(), order.end(), 0);
@@ -1183,12 +1234,11 @@ pt_status pt_batch_loglik_noalloc(pt_ctx *ctx, pt_aln *const *alns, int32_t n_al
     // workspace layout: the sections copied from the host, then the ones the
     // kernels write; each 256-byte aligned
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    const double ident[16] = {1, 0, 0, 0, 0, 1, 0, 0, 0, 0, 1, 0, 0, 0, 0, 1};
     const size_t o_aln = 0, o_tree = up(o_aln + sizeof(AlnDev) * B), o_ops = up(o_tree + sizeof(TreeDev) * B),
                  o_etree = up(o_ops + sizeof(Op) * ops.size()), o_ttree = up(o_etree + sizeof(int32_t) * NE),
-                 o_len = up(o_ttree + sizeof(int32_t) * tiles), o_ident = up(o_len + sizeof(double) * NE),
-                 in_bytes = o_ident + sizeof(ident), o_pm = up(in_bytes),
-                 o_part = up(o_pm + sizeof(double) * pm_off), o_lnl = up(o_part + sizeof(double) * 3 * tiles),
+                 o_len = up(o_ttree + sizeof(int32_t) * tiles), in_bytes = o_len + sizeof(double) * NE,
+                 o_pm = up(in_bytes), o_part = up(o_pm + sizeof(double) * pm_off),
+                 o_lnl = up(o_part + sizeof(double) * tiles),
                  total = o_lnl + sizeof(double) * B;
     if (total > pt::kNoAllocBytes)
         return fail(PT_ENOMEM, "batch needs " + std::to_string(total) + " bytes of the " +
@@ -1200,7 +1250,6 @@ pt_status pt_batch_loglik_noalloc(pt_ctx *ctx, pt_aln *const *alns, int32_t n_al
     std::memcpy(img.data() + o_etree, edge_tree.data(), sizeof(int32_t) * NE);
     std::memcpy(img.data() + o_ttree, tile_tree.data(), sizeof(int32_t) * tiles);
     std::memcpy(img.data() + o_len, brlen, sizeof(double) * NE);
-    std::memcpy(img.data() + o_ident, ident, sizeof(ident));
     char *ws = reinterpret_cast<char *>(ctx->noalloc);
     hipStream_t s = ctx->stream;
     PT_HIP(hipSetDevice(ctx->device));
@@ -1219,12 +1268,11 @@ pt_status pt_batch_loglik_noalloc(pt_ctx *ctx, pt_aln *const *alns, int32_t n_al
     a.part_cols = 1;
     a.kp = kp;
     a.reg_depth = depth;
-    a.ident = reinterpret_cast<const double *>(ws + o_ident);
+    a.reg_taxa = n_max;
     double *d_lnl = reinterpret_cast<double *>(ws + o_lnl);
     hipError_t e;
-    if ((e = pt::launch_pmat(a, reinterpret_cast<const double *>(ws + o_len), s)) != hipSuccess ||
-        (e = pt::launch_loglik_reg(kp, a, lds, s)) != hipSuccess ||
-        (e = pt::launch_reduce(false, a, d_lnl, nullptr, nullptr, s)) != hipSuccess)
+    if ((e = pt::launch_pmat_lanes(a, reinterpret_cast<const double *>(ws + o_len), max_E, s)) != hipSuccess ||
+        (e = pt::launch_prune(a, items, d_lnl, s)) != hipSuccess)
         return fail(PT_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(e));
     std::vector<double> out(B);
     PT_HIP(hipMemcpyAsync(out.data(), d_lnl, sizeof(double) * B, hipMemcpyDeviceToHost, s));

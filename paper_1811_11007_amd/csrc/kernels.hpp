@@ -12,6 +12,7 @@ struct BatchArgs {
     const AlnDev *alns;
     const Op *ops;
     const int32_t *tile_tree;   // tile kernels: owning tree of each tile
+    const int32_t *tile_of;     // register-resident lnL: each block's tile within its tree (null: in order)
     const int32_t *edge_tree;   // owning tree of each flat edge
     const int32_t *order;       // optimisation: tree order (largest first)
     void *clv;                  // float or double partials
@@ -29,7 +30,7 @@ struct BatchArgs {
     int32_t groups;             // optimisation: blocks per tree (1: one block per tree, work queue)
     unsigned long long *gsync;  // optimisation with groups > 1: per-tree cross-block words, zeroed
     int32_t reg_depth;          // register-resident lnL: stack slots of the deepest tree
-    const double *ident;        // register-resident lnL: the 4x4 identity (16 doubles)
+    int32_t reg_taxa;           // register-resident lnL: taxa of the largest tree
     long long wait_cycles;      // optimisation with groups > 1: shader clocks before a
                                 // cross-block wait gives up (0: kGroupWaitCycles)
 };
@@ -68,13 +69,16 @@ hipError_t launch_pmat(const BatchArgs &a, const double *brlen, hipStream_t s);
 bool tile_patterns_supported(int pats);
 hipError_t launch_tiles(int precision, int kp, int tile_pats, const BatchArgs &a, const double *brlen,
                         size_t lds_bytes, hipStream_t s);
-// Register-resident lnL (k_loglik_reg): patterns per tile for a padded
-// category count, its LDS for n taxa and a stack of `depth` slots, and the
-// launch (one block per tile; a.tile_tree, a.part, a.n_tiles and
-// a.reg_depth describe the register tiles; lds_bytes from loglik_reg_lds).
-int loglik_reg_tile_patterns(int kp);
-size_t loglik_reg_lds(int kp, int n, int depth);
-hipError_t launch_loglik_reg(int kp, const BatchArgs &a, size_t lds_bytes, hipStream_t s);
+// Register-resident lnL (k_prune): `items` matrix-core items per wave (2, 4
+// or 8, at most prune_max_items); patterns per tile, LDS bytes of a block for
+// trees of up to n taxa, the transition matrices in lane order, and the
+// launch with the tile sums (a.tile_tree, a.part, a.n_tiles, a.reg_depth and
+// a.reg_taxa describe the register tiles).
+int prune_max_items(int kp);
+int prune_tile_patterns(int kp, int items);
+size_t prune_lds(int kp, int items, int n);
+hipError_t launch_pmat_lanes(const BatchArgs &a, const double *brlen, int max_edges, hipStream_t s);
+hipError_t launch_prune(const BatchArgs &a, int items, double *lnl, hipStream_t s);
 // The fixed device workspace of pt_batch_loglik_noalloc (noalloc.hip):
 // kNoAllocBytes on each device; its address on `device`, looked up once per
 // device (with that device current) and kept.
@@ -82,6 +86,18 @@ constexpr size_t kNoAllocBytes = (size_t)64 << 20;
 hipError_t noalloc_workspace(int device, void **out);
 hipError_t launch_reduce(bool grad, const BatchArgs &a, double *lnl, double *grad_out,
                          double *hess_out, hipStream_t s);
+// The optimisation kernel at one (precision, block size).
+struct OptimizeShape {
+    int (*occupancy)(int kp, bool tab_lds, bool grouped, size_t lds);
+    size_t (*spill)(int kp, bool tab_lds, bool grouped);
+    hipError_t (*launch)(int kp, int items, bool tab_lds, int pm_doubles, int grid, const BatchArgs &a, double *brlen,
+                         const OptParams &opt, double *lnl, int32_t *passes, int32_t *status, size_t lds,
+                         hipStream_t s);
+};
+OptimizeShape optimize_f32_256();
+OptimizeShape optimize_f32_512();
+OptimizeShape optimize_f64_256();
+OptimizeShape optimize_f64_512();
 // With a.groups > 1, grid = trees x groups and a.gsync zeroed beforehand.
 hipError_t launch_optimize(int precision, int block, int kp, int items, bool tab_lds, int pm_doubles, int grid,
                            const BatchArgs &a, double *brlen, const OptParams &opt, double *lnl,

@@ -172,6 +172,7 @@ pt_status build_model(const pt_model &m, AlnDev &d, std::string &err) {
         }
     for (int k = 0; k < 4; ++k) d.lam[k] = lam[k];
     for (int i = 0; i < 4; ++i) d.freqs[i] = m.freqs[i];
+    d.log_k = std::log((double)d.K);
     return PT_OK;
 }
 

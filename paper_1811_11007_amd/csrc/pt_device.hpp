@@ -23,17 +23,17 @@ enum : int32_t {
     OP_NEWTON = 2,  // optimise the length of edge e between sides a and b
     OP_EVAL = 3,    // lnL (and derivatives) across edge e; out = output column
     // Register programs (the lnL with every partial kept in registers):
-    OP_RUPDATE = 4,  // acc = (P(ea) . side a) * (P(eb) . side b), then scaling
-    OP_RPUSH = 5,    // stack slot dst = acc
-    OP_REVAL = 6,    // lnL across edge eb: pi . (side a * (P(eb) . side b)); ea = -1
+    OP_RUPDATE = 4,  // acc = (P(ea) . side a) * (P(eb) . side b), then scaling; kept in
+                     // stack slot dst too when dst >= 0
+    OP_REVAL = 5,    // lnL across edge eb: pi . (side a * (P(eb) . side b)); ea = eb
 };
 
 // Side references of register programs: a leaf's tip (>= 0), the
 // accumulator, or stack slot REF_STACK0 - ref.
 constexpr int32_t REF_ACC = -1;
 constexpr int32_t REF_STACK0 = -2;
-constexpr int kRegStack = 8;      // stack slots of the register kernel
-constexpr int kRegStackRegs = 4;  // programs of at most this many slots keep the stack in registers
+constexpr int kRegStack = 8;  // stack slots of the register kernel
+constexpr int kRegAhead = 2;  // copies of a register program's last op that follow it
 
 struct Op {
     int32_t code;
@@ -43,7 +43,7 @@ struct Op {
                     // NEWTON: 1 when this step reports the tree's lnL
     int32_t b;      // side b
     int32_t eb;     // UPDATE: edge of side b
-    int32_t pad0, pad1;
+    int32_t tip_a, tip_b;  // register programs: the sides' leaves, 0 where a side is no tip
 };
 
 struct AlnDev {
@@ -56,6 +56,7 @@ struct AlnDev {
     double W[16];          // W_im = pi_i U_im = Uinv_mi = sqrt(pi_i) V_im
     double lam[4];
     double rate[kMaxCats]; // category rates (0 for padded categories)
+    double log_k;          // ln K
 };
 
 struct TreeDev {

@@ -203,6 +203,8 @@ int compile_loglik_reg(const Tree &t, std::vector<Op> &ops) {
         op.ea = ea;
         op.b = b;
         op.eb = eb;
+        op.tip_a = std::max(a, 0);
+        op.tip_b = std::max(b, 0);
         ops.push_back(op);
     };
     // Leaves the partial of v's side (seen from parent) in the accumulator,
@@ -212,32 +214,34 @@ int compile_loglik_reg(const Tree &t, std::vector<Op> &ops) {
         child_pair(v, parent, c, e);
         if (need(c[1], v) > need(c[0], v)) { std::swap(c[0], c[1]); std::swap(e[0], e[1]); }
         if (c[0] < n) {  // two tips
-            emit_op(OP_RUPDATE, 0, c[0], e[0], c[1], e[1]);
+            emit_op(OP_RUPDATE, -1, c[0], e[0], c[1], e[1]);
         } else if (c[1] < n) {
             emit(c[0], v, sp);
-            emit_op(OP_RUPDATE, 0, REF_ACC, e[0], c[1], e[1]);
+            emit_op(OP_RUPDATE, -1, REF_ACC, e[0], c[1], e[1]);
         } else {
             emit(c[0], v, sp);
-            emit_op(OP_RPUSH, sp, 0, 0, 0, 0);
+            ops.back().dst = sp;
             depth = std::max(depth, sp + 1);
             emit(c[1], v, sp + 1);
-            emit_op(OP_RUPDATE, 0, REF_STACK0 - sp, e[0], REF_ACC, e[1]);
+            emit_op(OP_RUPDATE, -1, REF_STACK0 - sp, e[0], REF_ACC, e[1]);
         }
     };
     int u = t.ends[0], v = t.ends[1];
     if (need(v, u) > need(u, v)) std::swap(u, v);  // u's side first
     if (u < n) {  // two tips (n = 2)
-        emit_op(OP_REVAL, 0, u, -1, v, 0);
+        emit_op(OP_REVAL, 0, u, 0, v, 0);
     } else if (v < n) {
         emit(u, v, 0);
-        emit_op(OP_REVAL, 0, REF_ACC, -1, v, 0);
+        emit_op(OP_REVAL, 0, REF_ACC, 0, v, 0);
     } else {
         emit(u, v, 0);
-        emit_op(OP_RPUSH, 0, 0, 0, 0, 0);
+        ops.back().dst = 0;
         depth = std::max(depth, 1);
         emit(v, u, 1);
-        emit_op(OP_REVAL, 0, REF_STACK0, -1, REF_ACC, 0);
+        emit_op(OP_REVAL, 0, REF_STACK0, 0, REF_ACC, 0);
     }
+    // the kernel reads two ops ahead
+    for (int k = 0; k < kRegAhead; ++k) ops.push_back(Op(ops.back()));
     return depth;
 }
 
