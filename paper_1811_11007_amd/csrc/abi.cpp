@@ -312,14 +312,15 @@ size_t stored_lds(int precision, int E, int kp) {
 }
 
 // Whether the register-resident lnL takes trees of up to n taxa and `depth`
-// stack slots: up to kRegStack slots, and a tile of tip codes that keeps
+// stack slots: up to eight slots, and a tile of tip codes that keeps
 // within the LDS of a block at 256 patterns for two or four padded
 // categories, 512 for one and 128 for eight (beyond four slots, less by 64
 // bytes per slot and lane).  The kernel itself needs less.
 bool reg_fits(const pt_ctx *ctx, int kp, int n, int depth) {
+    if (depth > 8) return false;
     const size_t waves = std::max(4, kp), pats = 128 * waves / kp;
     const size_t stack = depth <= 4 ? 0 : (size_t)depth * 2 * 64 * waves * 32;
-    return depth <= pt::kRegStack && stack + (size_t)n * pats <= ctx->lds_per_block;
+    return stack + (size_t)n * pats <= ctx->lds_per_block;
 }
 
 // The blocks' tiles, so that the tiles of a tree run on one XCD and find its
@@ -355,9 +356,10 @@ std::vector<int32_t> tiles_by_xcd(const std::vector<int> &order, const std::vect
 // needs the waves), in blocks that fit the LDS.  Measured at 2, 4 and 8
 // items: 48 trees of 27 taxa x 976 patterns (1464 waves at 8) 22.8, 19.1 and
 // 20.2 us; 512 trees over four alignments (16900 waves) 195, 150 and 141 us.
-int reg_items(const pt_ctx *ctx, int kp, int n, int64_t patterns) {
+int reg_items(const pt_ctx *ctx, int kp, int n, int depth, int64_t patterns) {
     const int64_t want = 8LL * std::max(1, ctx->n_cu);
     int items = pt::prune_max_items(kp);
+    if (depth > 3) items /= 2;  // (more would need scratch memory)
     while (items > 2 && (patterns / (pt::prune_tile_patterns(kp, items) / 4) < want ||
                          pt::prune_lds(kp, items, n) > ctx->lds_per_block))
         items /= 2;
@@ -521,9 +523,12 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
         std::string err;
         int E = 0, n_slots = 0, reg_depth = 0;
         bool any = true, stored_ok = true;
-        std::vector<Op> ll, gr, p1, p2, p3, rg;
+        std::vector<Op> ll, gr, p1, p2, rg;
     };
-    const bool want_reg = (kinds & PT_PLAN_LOGLIK) || ((kinds & PT_PLAN_GRAD) && precision == PT_FP32);
+    // an optimisation with FP32 partials reports the register-resident lnL at
+    // its final lengths
+    const bool opt_lnl = (kinds & PT_PLAN_OPTIMIZE) && precision == PT_FP32;
+    const bool want_reg = (kinds & PT_PLAN_LOGLIK) || ((kinds & PT_PLAN_GRAD) && precision == PT_FP32) || opt_lnl;
     std::vector<Compiled> cp(B);
     auto compile_tree = [&](int b) {
         Compiled &c = cp[b];
@@ -562,8 +567,7 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
             c.any = !m;
             for (int e = 0; m && e < c.E; ++e) c.any |= m[e] != 0;
             if (c.any) pt::compile_optimize(t, m, c.p1, c.p2);
-            else pt::compile_loglik(t, c.p1);
-            if (precision == PT_FP32) pt::compile_loglik_dense(t, c.p3);
+            else if (precision == PT_FP64) pt::compile_loglik(t, c.p1);  // FP32: see opt_lnl
         }
     };
     {
@@ -593,9 +597,14 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
     int64_t reg_patterns = 0;
     for (int b = 0; b < B; ++b) reg_patterns += alns[trees->aln_index[b]]->P;
     if (!reg_fits(ctx, kp, reg_n, reg_depth)) pl->reg_ok = false;
+    // (every tree the optimisation takes fits the kernel itself: its matrices
+    // in LDS bound it to about a thousand taxa)
+    if (opt_lnl && B > 0 && (reg_depth > pt::kRegStack || pt::prune_lds(kp, 2, reg_n) > ctx->lds_per_block))
+        return fail(PT_EINTERNAL, "a tree exceeds the likelihood kernel");
+    const bool reg_built = pl->reg_ok || (opt_lnl && B > 0);
     pl->reg_depth = reg_depth;
     pl->reg_taxa = reg_n;
-    pl->reg_items = reg_items(ctx, kp, reg_n, reg_patterns);
+    pl->reg_items = reg_items(ctx, kp, reg_n, reg_depth, reg_patterns);
     const int reg_pats = pt::prune_tile_patterns(kp, pl->reg_items);
     pl->stored_ok = true;
     for (int b = 0; b < B; ++b) pl->stored_ok = pl->stored_ok && cp[b].stored_ok;
@@ -630,29 +639,27 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
             count = (int32_t)v.size();
             ops.insert(ops.end(), v.begin(), v.end());
         };
-        if (pl->reg_ok) {
+        if (reg_built) {
             treg[b] = base;
             treg[b].n_tiles = (ad.P + reg_pats - 1) / reg_pats;
             append(c.rg, treg[b].op_first, treg[b].n_first);
-            treg[b].n_first -= pt::kRegAhead;
         }
         if (kinds & PT_PLAN_LOGLIK) append(c.ll, tll[b].op_first, tll[b].n_first);
         if (kinds & PT_PLAN_GRAD) append(c.gr, tgr[b].op_first, tgr[b].n_first);
         if (kinds & PT_PLAN_OPTIMIZE) {
             append(c.p1, top[b].op_first, top[b].n_first);
             append(c.p2, top[b].op_steady, top[b].n_steady);
-            if (precision == PT_FP32) append(c.p3, top[b].op_final, top[b].n_final);
             cost[b] = (double)ad.P * ad.K * (double)(c.p2.size() + 1);
         }
         std::vector<Op>().swap(c.ll);
         std::vector<Op>().swap(c.gr);
         std::vector<Op>().swap(c.p1);
         std::vector<Op>().swap(c.p2);
-        std::vector<Op>().swap(c.p3);
         std::vector<Op>().swap(c.rg);
     }
+    ops.resize(ops.size() + pt::kRegAhead);
     std::vector<int32_t> tile_tree_reg;
-    if (pl->reg_ok) {
+    if (reg_built) {
         // register tiles of the longest programs first, as below
         std::vector<int> order(B);
         for (int b = 0; b < B; ++b) order[b] = b;
@@ -710,7 +717,7 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
     if (kinds & PT_PLAN_LOGLIK) if ((st = up_trees(tll, &pl->d_trees_ll))) return st;
     if (kinds & PT_PLAN_GRAD) if ((st = up_trees(tgr, &pl->d_trees_gr))) return st;
     if (kinds & PT_PLAN_OPTIMIZE) if ((st = up_trees(top, &pl->d_trees_opt))) return st;
-    if (pl->reg_ok) {
+    if (reg_built) {
         if ((st = up_trees(treg, &pl->d_trees_reg))) return st;
         if ((st = dev_alloc(pl.get(), &pl->d_tile_tree_reg, sizeof(int32_t) * tile_tree_reg.size()))) return st;
         PT_HIP(hipMemcpy(pl->d_tile_tree_reg, tile_tree_reg.data(), sizeof(int32_t) * tile_tree_reg.size(),
@@ -795,6 +802,18 @@ pt::BatchArgs batch_args(const pt_plan *pl, const TreeDev *trees, int part_cols)
     return a;
 }
 
+// The same for the register-resident lnL.
+pt::BatchArgs reg_args(const pt_plan *pl) {
+    pt::BatchArgs r = batch_args(pl, pl->d_trees_reg, 1);
+    r.tile_tree = pl->d_tile_tree_reg;
+    r.tile_of = pl->d_tile_tree_reg + pl->n_tiles_reg;
+    r.part = pl->d_part_reg;
+    r.n_tiles = pl->n_tiles_reg;
+    r.reg_depth = pl->reg_depth;
+    r.reg_taxa = pl->reg_taxa;
+    return r;
+}
+
 // Enqueue the kernels of one plan call.
 pt_status enqueue(pt_plan *pl, int kind, const double *brlen_c, double *brlen, const pt::OptParams *op,
                   double *lnl, int32_t *passes, int32_t *status, double *grad, double *hess, hipStream_t s) {
@@ -815,13 +834,7 @@ pt_status enqueue(pt_plan *pl, int kind, const double *brlen_c, double *brlen, c
         // (FP32 storage puts ~1e-4 of rounding noise into lnL at a few
         // thousand sites; the gradient keeps its stored partials)
         if (reg_ll || (g && pl->reg_ok && pl->precision == PT_FP32)) {
-            pt::BatchArgs r = batch_args(pl, pl->d_trees_reg, 1);
-            r.tile_tree = pl->d_tile_tree_reg;
-            r.tile_of = pl->d_tile_tree_reg + pl->n_tiles_reg;
-            r.part = pl->d_part_reg;
-            r.n_tiles = pl->n_tiles_reg;
-            r.reg_depth = pl->reg_depth;
-            r.reg_taxa = pl->reg_taxa;
+            pt::BatchArgs r = reg_args(pl);
             if ((e = pt::launch_pmat_lanes(r, brlen_c, pl->max_E, s)) != hipSuccess) goto bad;
             if ((e = pt::launch_prune(r, pl->reg_items, lnl, s)) != hipSuccess) goto bad;
         }
@@ -842,6 +855,16 @@ pt_status enqueue(pt_plan *pl, int kind, const double *brlen_c, double *brlen, c
         if ((e = pt::launch_optimize(pl->precision, pl->opt_block, pl->kp, pl->opt_items, pl->opt_tab_lds, pl->pm_doubles,
                                      pl->opt_grid, a, brlen, *op, lnl, passes, status, pl->lds_opt, s)) != hipSuccess)
             goto bad;
+        if (pl->precision == PT_FP32) {
+            // lnL at the final lengths, with no partial stored; a tree whose
+            // wait timed out keeps its NaN
+            pt::BatchArgs r = reg_args(pl);
+            r.prior_rate = op->prior_rate;
+            r.keep_nan = 1;
+            if ((e = pt::launch_pmat_lanes(r, brlen, pl->max_E, s)) != hipSuccess) goto bad;
+            r.brlen = brlen;
+            if ((e = pt::launch_prune(r, pl->reg_items, lnl, s)) != hipSuccess) goto bad;
+        }
         return PT_OK;
     }
 bad:
@@ -1188,7 +1211,7 @@ pt_status pt_batch_loglik_noalloc(pt_ctx *ctx, pt_aln *const *alns, int32_t n_al
     std::vector<Op> ops;
     std::vector<TreeDev> td(B);
     std::vector<AlnDev> ad(B);
-    std::vector<int32_t> edge_tree(NE), tile_tree;
+    std::vector<int32_t> tile_tree;
     std::vector<int> tree_E(B);
     int depth = 0, n_max = 0, max_E = 0;
     int64_t pm_off = 0, patterns = 0;
@@ -1196,7 +1219,6 @@ pt_status pt_batch_loglik_noalloc(pt_ctx *ctx, pt_aln *const *alns, int32_t n_al
         n_max = std::max(n_max, ntx[b]);
         patterns += alns[trees->aln_index[b]]->P;
     }
-    const int items = reg_items(ctx, kp, n_max, patterns), reg_pats = pt::prune_tile_patterns(kp, items);
     for (int b = 0; b < B; ++b) {
         pt::Tree t;
         std::string err;
@@ -1210,36 +1232,47 @@ pt_status pt_batch_loglik_noalloc(pt_ctx *ctx, pt_aln *const *alns, int32_t n_al
         d.pm_off = pm_off;
         d.op_first = (int32_t)ops.size();
         depth = std::max(depth, pt::compile_loglik_reg(t, ops));
-        d.n_first = (int32_t)ops.size() - d.op_first - pt::kRegAhead;
-        d.n_tiles = (a.P + reg_pats - 1) / reg_pats;
+        d.n_first = (int32_t)ops.size() - d.op_first;
         td[b] = d;
         ad[b] = a;
         tree_E[b] = t.n_edges;
         max_E = std::max(max_E, t.n_edges);
         pm_off += (int64_t)t.n_edges * kp * 16;
-        for (int e = 0; e < t.n_edges; ++e) edge_tree[d.edge_off + e] = b;
     }
-    if (depth > pt::kRegStack) return fail(PT_EUNSUPPORTED, "a tree needs more than 8 stack slots");
+    ops.resize(ops.size() + pt::kRegAhead);
+    if (depth > 8) return fail(PT_EUNSUPPORTED, "a tree needs more than 8 stack slots");
     if (!reg_fits(ctx, kp, n_max, depth)) return fail(PT_EUNSUPPORTED, "a tree exceeds the LDS of a block");
-    {   // tiles of the trees with the most edges first
-        std::vector<int> order(B);
-        std::iota(order.begin(), order.end(), 0);
-        std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return tree_E[x] > tree_E[y]; });
-        for (int b : order) {
-            td[b].tile_begin = (int32_t)tile_tree.size();
-            for (int x = 0; x < td[b].n_tiles; ++x) tile_tree.push_back(b);
-        }
-    }
-    const int tiles = (int)tile_tree.size();
+    // tiles of the trees with the most edges first
+    std::vector<int> order(B);
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return tree_E[x] > tree_E[y]; });
     // workspace layout: the sections copied from the host, then the ones the
-    // kernels write; each 256-byte aligned
+    // kernels write; each 256-byte aligned.  A batch that only just fits takes
+    // the most items per wave, and so the fewest tiles.
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t o_aln = 0, o_tree = up(o_aln + sizeof(AlnDev) * B), o_ops = up(o_tree + sizeof(TreeDev) * B),
-                 o_etree = up(o_ops + sizeof(Op) * ops.size()), o_ttree = up(o_etree + sizeof(int32_t) * NE),
-                 o_len = up(o_ttree + sizeof(int32_t) * tiles), in_bytes = o_len + sizeof(double) * NE,
-                 o_pm = up(in_bytes), o_part = up(o_pm + sizeof(double) * pm_off),
-                 o_lnl = up(o_part + sizeof(double) * tiles),
-                 total = o_lnl + sizeof(double) * B;
+                 o_ttree = up(o_ops + sizeof(Op) * ops.size());
+    int items = reg_items(ctx, kp, n_max, depth, patterns), tiles = 0;
+    size_t o_len = 0, in_bytes = 0, o_pm = 0, o_part = 0, o_lnl = 0, total = 0;
+    for (;; items *= 2) {
+        const int pats = pt::prune_tile_patterns(kp, items);
+        tiles = 0;
+        for (int b : order) {
+            td[b].n_tiles = (ad[b].P + pats - 1) / pats;
+            td[b].tile_begin = tiles;
+            tiles += td[b].n_tiles;
+        }
+        o_len = up(o_ttree + sizeof(int32_t) * tiles);
+        in_bytes = o_len + sizeof(double) * NE;
+        o_pm = up(in_bytes);
+        o_part = up(o_pm + sizeof(double) * pm_off);
+        o_lnl = up(o_part + sizeof(double) * tiles);
+        total = o_lnl + sizeof(double) * B;
+        if (total <= pt::kNoAllocBytes || 2 * items > pt::prune_max_items(kp) ||
+            pt::prune_lds(kp, 2 * items, n_max) > ctx->lds_per_block)
+            break;
+    }
+    for (int b : order) tile_tree.insert(tile_tree.end(), td[b].n_tiles, b);
     if (total > pt::kNoAllocBytes)
         return fail(PT_ENOMEM, "batch needs " + std::to_string(total) + " bytes of the " +
                                    std::to_string(pt::kNoAllocBytes) + "-byte no-allocation workspace");
@@ -1247,7 +1280,6 @@ pt_status pt_batch_loglik_noalloc(pt_ctx *ctx, pt_aln *const *alns, int32_t n_al
     std::memcpy(img.data() + o_aln, ad.data(), sizeof(AlnDev) * B);
     std::memcpy(img.data() + o_tree, td.data(), sizeof(TreeDev) * B);
     std::memcpy(img.data() + o_ops, ops.data(), sizeof(Op) * ops.size());
-    std::memcpy(img.data() + o_etree, edge_tree.data(), sizeof(int32_t) * NE);
     std::memcpy(img.data() + o_ttree, tile_tree.data(), sizeof(int32_t) * tiles);
     std::memcpy(img.data() + o_len, brlen, sizeof(double) * NE);
     char *ws = reinterpret_cast<char *>(ctx->noalloc);
@@ -1258,7 +1290,6 @@ pt_status pt_batch_loglik_noalloc(pt_ctx *ctx, pt_aln *const *alns, int32_t n_al
     a.trees = reinterpret_cast<const TreeDev *>(ws + o_tree);
     a.alns = reinterpret_cast<const AlnDev *>(ws + o_aln);
     a.ops = reinterpret_cast<const Op *>(ws + o_ops);
-    a.edge_tree = reinterpret_cast<const int32_t *>(ws + o_etree);
     a.tile_tree = reinterpret_cast<const int32_t *>(ws + o_ttree);
     a.pmat = reinterpret_cast<double *>(ws + o_pm);
     a.part = reinterpret_cast<double *>(ws + o_part);

@@ -31,6 +31,9 @@ struct BatchArgs {
     unsigned long long *gsync;  // optimisation with groups > 1: per-tree cross-block words, zeroed
     int32_t reg_depth;          // register-resident lnL: stack slots of the deepest tree
     int32_t reg_taxa;           // register-resident lnL: taxa of the largest tree
+    int32_t keep_nan;           //   a tree whose lnL output is NaN keeps it
+    double prior_rate;          //   > 0: plus the log prior of the lengths `brlen`
+    const double *brlen;
     long long wait_cycles;      // optimisation with groups > 1: shader clocks before a
                                 // cross-block wait gives up (0: kGroupWaitCycles)
 };

@@ -79,14 +79,11 @@ __global__ void __launch_bounds__(BS) k_optimize(const BatchArgs a, double *brle
         const AlnDev *aln = a.alns + td.aln;
         const int E = td.n_edges;
         // FP64 partials: the matrices, then the lengths, in LDS.  FP32
-        // partials: the lengths, then (16-byte aligned) an FP32 copy of the
-        // matrices for the loop's updates in LDS, while the FP64 matrices,
-        // read only by the final FP64 evaluation, are written once before it
-        // to this tree's slice of the global matrix buffer (so a 64-taxon
-        // tree's table still fits in LDS beside the FP32 copy).
+        // partials: the lengths, then (16-byte aligned) the matrices in FP32
+        // (so a 64-taxon tree's table still fits in LDS beside them).
         constexpr bool kF32 = std::is_same<T, float>::value;
         constexpr bool kFuseUpd = GRP && TAB_LDS && FuseFirst<KP>::value && BS == 256;
-        double *pm = kF32 ? a.pmat + td.pm_off : lds;
+        double *pm = kF32 ? nullptr : lds;
         double *tl = kF32 ? lds : lds + (size_t)E * KP * 16;
         float *pmf = reinterpret_cast<float *>(lds + (((size_t)E + 1) & ~(size_t)1));
         for (int e = tid; e < E; e += BS) tl[e] = fmin(fmax(brlen[td.edge_off + e], opt.t_min), opt.t_max);
@@ -161,11 +158,13 @@ __global__ void __launch_bounds__(BS) k_optimize(const BatchArgs a, double *brle
                 }
                 const int e = op.dst;
                 const double t0 = tl[e];
-                if (op.code == OP_EVAL) {
-                    const Sums3 r = eval_edge<T, BS, KP>(v, op.a, op.b, 0, ni, t0, red, wx, parity, gs);
-                    parity = r.parity;
-                    cur = r.l0;
-                    continue;
+                if constexpr (kPassLnl<T>) {
+                    if (op.code == OP_EVAL) {
+                        const Sums3 r = eval_edge<T, BS, KP>(v, op.a, op.b, 0, ni, t0, red, wx, parity, gs);
+                        parity = r.parity;
+                        cur = r.l0;
+                        continue;
+                    }
                 }
                 // the pass's lnL comes from its last edge step (op.ea = 1)
                 const EdgeResult r =
@@ -230,7 +229,7 @@ __global__ void __launch_bounds__(BS) k_optimize(const BatchArgs a, double *brle
                 }
             }
             ++passes;
-            cur += log_prior(tl, E, opt.prior_rate);
+            if constexpr (kPassLnl<T>) cur += log_prior(tl, E, opt.prior_rate);
             const double rise = kF32 ? pass_gain : cur - prev;
             if (td.n_steady == 0 || (rise < opt.tol_lnl && max_rel < opt.tol_t)) {
                 converged = true;
@@ -238,57 +237,6 @@ __global__ void __launch_bounds__(BS) k_optimize(const BatchArgs a, double *brle
             }
             if (passes >= opt.max_passes) break;
             prev = cur;
-        }
-        if (kF32 && td.n_final > 0) {
-            // The FP64 matrices at the final lengths, for the FP64 pass below
-            // (the loop's updates read only the FP32 copy in LDS, so no FP64
-            // matrix is stored during the loop).  Every block of a tree
-            // computes the same values from the same lengths.
-            for (int x = tid; x < E * KP * 16; x += BS) {
-                const int e = x / (KP * 16), r = x % (KP * 16);
-                pm[x] = pm_entry(&model, r >> 4, r & 15, tl[e]);
-            }
-            if (!GRP) __syncthreads();
-        }
-        if (GRP && kF32 && td.n_final > 0) {
-            // The FP64 pass below reuses the tree's buffer in another layout,
-            // so a block writes bytes that another block wrote as FP32
-            // partials.  The XCDs' L2 caches are not coherent: a dirty FP32
-            // line left in another XCD's L2 could later be written back over
-            // the new FP64 values.  Every wave writes back its L2 (release at
-            // device scope) and the group meets once before any FP64 write.
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            double z0 = 0.0, z1 = 0.0, z2 = 0.0;
-            group_sum3<BS>(z0, z1, z2, red, parity, gs);
-        }
-        if (std::is_same<T, float>::value && td.n_final > 0) {
-            // Report lnL from FP64 partials at the final lengths: one post-order
-            // pass over the same buffer (dense slots; the FP32 partials are no
-            // longer needed, and each thread touches only its own patterns).
-            TreeView<double> vd;
-            vd.m = v.m;
-            vd.pm = v.pm;
-            vd.tips = v.tips;
-            vd.w = v.w;
-            // the same share in the FP64 layout: every block of the tree has
-            // finished reading FP32 partials (their reads preceded the
-            // arrivals at the last reduction)
-            vd.clv = reinterpret_cast<double *>(reinterpret_cast<T *>(a.clv) + td.clv_off) + (size_t)lo * 4;
-            vd.cnt = v.cnt;
-            vd.P = v.P;
-            vd.np = v.np;
-            vd.K = v.K;
-            for (int o = 0; o < td.n_final; ++o) {
-                const Op op = load_op(a.ops, td.op_final + o);
-                if (op.code == OP_UPDATE) {
-                    do_update<double, BS, KP, kPmGlobal>(vd, op, 0, ni);
-                } else {
-                    const Sums3 r =
-                        eval_edge<double, BS, KP>(vd, op.a, op.b, 0, ni, tl[op.dst], red, wx, parity, gs);
-                    parity = r.parity;
-                    cur = r.l0 + log_prior(tl, E, opt.prior_rate);
-                }
-            }
         }
         if (g == 0) {
             for (int e = tid; e < E; e += BS) brlen[td.edge_off + e] = tl[e];
@@ -300,7 +248,7 @@ __global__ void __launch_bounds__(BS) k_optimize(const BatchArgs a, double *brle
             if (tid == 0) {
                 // a timed-out wait anywhere in the group: status 2, lnL NaN
                 const bool broken = GRP && load_agent(gsh.broken) != 0ull;
-                lnl_out[b] = broken ? NAN : cur;
+                lnl_out[b] = broken ? NAN : kPassLnl<T> ? cur : 0.0;
                 if (passes_out) passes_out[b] = passes;
                 if (status_out) status_out[b] = broken ? 2 : (converged ? 0 : 1);
             }

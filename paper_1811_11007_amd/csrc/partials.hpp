@@ -76,6 +76,7 @@ struct ModelS {
     double lam[4];
     double rate[kMaxCats];
     float Wf[16];    // W rounded to FP32 (the FP32 tables of the optimisation loop)
+    double log_k;    // ln K
 };
 
 __device__ inline void model_to_lds(const AlnDev *aln, ModelS *m) {
@@ -85,6 +86,7 @@ __device__ inline void model_to_lds(const AlnDev *aln, ModelS *m) {
         m->U[x] = aln->U[x];
         m->Uinv[x] = aln->Uinv[x];
     }
+    if (threadIdx.x == 0) m->log_k = aln->log_k;
     if (threadIdx.x < 4) m->lam[threadIdx.x] = aln->lam[threadIdx.x];
     if (threadIdx.x < kMaxCats) m->rate[threadIdx.x] = aln->rate[threadIdx.x];
 }
@@ -293,20 +295,16 @@ __device__ inline void group_sum3(double &a, double &b, double &c, double *red, 
 // wave complete in order, so the wave's later reads see them.
 constexpr int kWx = 3 * 4 * kMaxCats;  // doubles per wave
 
-__device__ inline void wave_expo(double *wx, const ModelS *md, int K, double t, float *wxf = nullptr) {
+template <typename X>  // float: the same values rounded
+__device__ inline void wave_expo(X *wx, const ModelS *md, int K, double t) {
     const int lane = threadIdx.x & 63;
     if (lane < 4 * K) {
         const int k = lane >> 2, m = lane & 3;
         const double q = md->lam[m] * md->rate[k];
         const double e = exp(q * t);
-        wx[lane] = e;
-        wx[4 * kMaxCats + lane] = e * q;
-        wx[8 * kMaxCats + lane] = e * q * q;
-        if (wxf) {
-            wxf[lane] = (float)e;
-            wxf[4 * kMaxCats + lane] = (float)(e * q);
-            wxf[8 * kMaxCats + lane] = (float)(e * q * q);
-        }
+        wx[lane] = (X)e;
+        wx[4 * kMaxCats + lane] = (X)(e * q);
+        wx[8 * kMaxCats + lane] = (X)(e * q * q);
     }
     __builtin_amdgcn_wave_barrier();
 }
@@ -357,9 +355,7 @@ struct Side {
 //   kPmLds32  FP32 copy in LDS (half the broadcast bytes), for FP32 partials
 //             in the optimisation loop, whose updates then compute in FP32
 //             (update_pattern_f32).
-//   kPmGlobal FP64 matrices in global memory (the FP64 evaluation that ends
-//             an optimisation with FP32 partials).
-enum : int { kPmLds = 0, kPmConst = 1, kPmLds32 = 2, kPmGlobal = 3 };
+enum : int { kPmLds = 0, kPmConst = 1, kPmLds32 = 2 };
 template <int PM>
 struct PmPtr {
     using type = const double *;
@@ -371,10 +367,6 @@ struct PmPtr<kPmConst> {
 template <>
 struct PmPtr<kPmLds32> {
     using type = const float *;
-};
-template <>
-struct PmPtr<kPmGlobal> {
-    using type = const __attribute__((address_space(1))) double *;
 };
 template <int PM, typename V>
 __device__ inline typename PmPtr<PM>::type pm_base(const V &v) {
@@ -646,7 +638,7 @@ template <typename T, int BS, int KP>
 __device__ inline Sums3 eval_edge(const TreeView<T> &v, int a, int b, int base, int ni, double t, double *red,
                                   double *wx, int parity, GroupS *gs = nullptr, bool want_l0 = true) {
     wave_expo(wx, v.m, v.K, t);
-    const double logK = log((double)v.K);
+    const double logK = v.m->log_k;
     Sums3 r;
     r.l0 = r.l1 = r.l2 = 0.0;
     if (a < 0) {
@@ -660,6 +652,17 @@ __device__ inline Sums3 eval_edge(const TreeView<T> &v, int a, int b, int base, 
     r.parity = parity;
     return r;
 }
+
+// Whether the optimisation loop evaluates lnL at the end of a pass: with FP64
+// partials the pass rule needs it; with FP32 partials the rule uses the
+// steps' model values, and lnL is evaluated once, at the final lengths, by
+// the register-resident pass (k_prune).  (A last pass of this kernel over FP64
+// partials stored in the tree's buffer, and a pass lnL that nothing read, cost
+// 16.3 against 8.6 ms a batch of 1024 radius-0 proposals of 64 taxa x 1711
+// patterns, mostly that pass's 28 GB of traffic, 25.6 against 20.8 ms for 256
+// trees over four alignments and 5.26 against 4.81 ms for 48 of 27 taxa.)
+template <typename T>
+constexpr bool kPassLnl = std::is_same<T, double>::value;
 
 struct EdgeResult {
     double t, lnl;
@@ -682,7 +685,7 @@ __device__ inline void table_row(const TreeView<T> &v, const SA &sa, const SB &s
                                  double *wrow, double w, double logK, const X *wxe, double &cterm, double &f1,
                                  double &f2) {
     const ModelS *md = v.m;
-    cterm += w * const_term<T>(sa.c + sb.c, logK);
+    if constexpr (kPassLnl<T>) cterm += w * const_term<T>(sa.c + sb.c, logK);
     wrow[p] = w;
     double L = 0.0, L1 = 0.0, L2 = 0.0;
 #pragma unroll
@@ -739,7 +742,7 @@ __device__ inline double table_sides(const TreeView<T> &v, int a, int b, int ni,
         sa1.fetch(v, a, p1);
         sb1.fetch(v, b, p1);
         const double w0 = ldg(v.w + p0), w1 = ldg(v.w + p1);
-        cterm += w0 * const_term<T>(sa0.c + sb0.c, logK);
+        if constexpr (kPassLnl<T>) cterm += w0 * const_term<T>(sa0.c + sb0.c, logK);
         wrow[p0] = w0;
         double L = 0.0, L1 = 0.0, L2 = 0.0;
 #pragma unroll
@@ -765,7 +768,7 @@ __device__ inline double table_sides(const TreeView<T> &v, int a, int b, int ni,
             f2 += w0 * (L2 * ia - r1 * r1);
         }
         if (two) {
-            cterm += w1 * const_term<T>(sa1.c + sb1.c, logK);
+            if constexpr (kPassLnl<T>) cterm += w1 * const_term<T>(sa1.c + sb1.c, logK);
             wrow[p1] = w1;
             double M = 0.0, M1 = 0.0, M2 = 0.0;
 #pragma unroll
@@ -931,7 +934,7 @@ first_expo(const TreeView<T> &v, double t, double *wx, float *wxf) {
     constexpr bool kF = std::is_same<T, float>::value;
     using XE = typename std::conditional<kF, float, double>::type;
     if constexpr (FuseFirst<KP>::value) {
-        if constexpr (kF) wave_expo(wx, v.m, v.K, t, wxf);
+        if constexpr (kF) wave_expo(wxf, v.m, v.K, t);
         else wave_expo(wx, v.m, v.K, t);
     }
     return kF ? reinterpret_cast<const XE *>(wxf) : reinterpret_cast<const XE *>(wx);
@@ -945,7 +948,7 @@ __device__ inline EdgePre update_and_table(const TreeView<T> &v, const Op &op, i
                                            double *wrow, double *wx, float *wxf) {
     constexpr bool kFuse = FuseFirst<KP>::value;
     const auto *wxe = first_expo<T, KP>(v, t, wx, wxf);
-    const double logK = log((double)v.K);
+    const double logK = v.m->log_k;
     EdgePre pre;
     pre.f1 = pre.f2 = 0.0;
 #define PT_UT(TA, TB, TO)                                                                                        \
@@ -989,7 +992,7 @@ __device__ inline EdgePre update_and_table(const TreeView<T> &v, const Op &op, i
 //  - the returned t is t_in + relax * (t_newton - t_in), kept in
 //    [t_min, t_max], when that step exceeds tol_t * max(t_in, 1e-6), else
 //    the Newton result;
-//  - with want_lnl, lnL is evaluated at the returned t.
+//  - with want_lnl, lnL is evaluated at the returned t (FP64 partials).
 // All threads hold identical block totals, so every thread takes the same
 // decisions.
 template <typename T, int BS, int KP, bool PAIR = true>
@@ -999,7 +1002,7 @@ __device__ inline EdgeResult newton_edge(const TreeView<T> &v, int a, int b, dou
                                          const EdgePre *pre = nullptr) {
     const double t_in = t;
     const size_t rows = (size_t)BS * ni;
-    const double logK = log((double)v.K);
+    const double logK = v.m->log_k;
     const long long c0 = clock64();
     constexpr bool kFuse = FuseFirst<KP>::value;
     double f1 = 0.0, f2 = 0.0;
@@ -1031,8 +1034,8 @@ __device__ inline EdgeResult newton_edge(const TreeView<T> &v, int a, int b, dou
             d2 = f2;
         } else if constexpr (std::is_same<T, float>::value) {
             // FP32 partials: FP32 exponentials suffice for the derivatives
-            // (they only steer Newton); lnL below uses FP64 ones
-            wave_expo(wx, v.m, v.K, t, wxf);
+            // (they only steer Newton)
+            wave_expo(wxf, v.m, v.K, t);
 #pragma unroll 1
             for (int j = 0; j < nj; j += 2)
                 newton_rows2<T, KP>(tab, wrow, rows, j * BS + threadIdx.x,
@@ -1077,7 +1080,7 @@ __device__ inline EdgeResult newton_edge(const TreeView<T> &v, int a, int b, dou
     if (relax != 1.0 && fabs(t - t_in) > opt.tol_t * fmax(t_in, 1e-6))
         t = fmin(fmax(t_in + relax * (t - t_in), opt.t_min), opt.t_max);
     double lnl = 0.0;
-    if (want_lnl) {
+    if (kPassLnl<T> && want_lnl) {
         wave_expo(wx, v.m, v.K, t);
         double l0 = cterm, z1 = 0.0, z2 = 0.0;
 #pragma unroll 1

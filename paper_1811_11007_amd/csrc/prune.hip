@@ -272,7 +272,7 @@ k_prune(const BatchArgs a) {
         };
         // The next op's matrices and tip codes are loaded while this one runs,
         // and the op after it, so that their addresses are known in time.
-        // (The root's op ends the program and is followed by two copies.)
+        // (The op read past the root's, which ends the program, is not used.)
         const Op *prog = a.ops + td.op_first;
         Op op = load_op(prog, 0), nx = load_op(prog, 1);
         double ma[NQ], mb[NQ];
@@ -436,6 +436,14 @@ __global__ void k_tile_sums(const BatchArgs a, double *lnl) {
         for (int u = 0; u < 8; ++u) s += v[u];
     }
     for (; t < n; ++t) s += p[t];
+    if (a.keep_nan && isnan(lnl[b])) return;
+    if (a.prior_rate > 0.0) {
+        // independent Exponential(rate) priors: sum_e (log rate - rate t_e)
+        const double lr = log(a.prior_rate);
+        double q = 0.0;
+        for (int e = 0; e < a.trees[b].n_edges; ++e) q += lr - a.prior_rate * a.brlen[a.trees[b].edge_off + e];
+        s += q;
+    }
     lnl[b] = s;
 }
 

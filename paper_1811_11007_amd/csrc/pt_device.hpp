@@ -32,8 +32,8 @@ enum : int32_t {
 // accumulator, or stack slot REF_STACK0 - ref.
 constexpr int32_t REF_ACC = -1;
 constexpr int32_t REF_STACK0 = -2;
-constexpr int kRegStack = 8;  // stack slots of the register kernel
-constexpr int kRegAhead = 2;  // copies of a register program's last op that follow it
+constexpr int kRegStack = 10;  // stack slots of the register kernel
+constexpr int kRegAhead = 1;  // ops past a register program's last that the kernel may load (never uses)
 
 struct Op {
     int32_t code;
@@ -71,8 +71,6 @@ struct TreeDev {
     int64_t edge_off;      // first edge in the flat per-edge arrays
     int64_t pm_off;        // first double of this tree's transition matrices
     int32_t tile_begin;    // first global tile index of this tree
-    int32_t op_final;      // FP32 optimisation: FP64 lnL program run at the end
-    int32_t n_final;       //   (slots renumbered densely, see tree.cpp)
     int32_t pad;
 };
 

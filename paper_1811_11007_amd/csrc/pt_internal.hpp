@@ -30,10 +30,6 @@ pt_status build_tree(int n, const int32_t *edges, Tree &t, std::string &err);
 // Programs (sequences of Op) executed by the kernels, one per tree.
 // lnL across one edge: the n-2 updates that make both sides valid, then EVAL.
 void compile_loglik(const Tree &t, std::vector<Op> &ops);
-// The same with the n-2 slots it uses renumbered 0..n-3, so the program fits
-// in two thirds of a tree's partial buffer at twice the element size (the
-// FP64 evaluation that ends an FP32 optimisation reuses the FP32 buffer).
-void compile_loglik_dense(const Tree &t, std::vector<Op> &ops);
 // lnL as a register program (OP_RUPDATE / OP_REVAL, rooted on
 // edge 0); returns the stack slots it needs.
 int compile_loglik_reg(const Tree &t, std::vector<Op> &ops);

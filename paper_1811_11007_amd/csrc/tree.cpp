@@ -151,26 +151,6 @@ void compile_loglik(const Tree &t, std::vector<Op> &ops) {
     ops.push_back(edge_op(OP_EVAL, 0, ra, rb, 0));
 }
 
-void compile_loglik_dense(const Tree &t, std::vector<Op> &ops) {
-    std::vector<Op> p;
-    compile_loglik(t, p);
-    std::vector<int> id(t.n_slots(), -1);
-    int next = 0;
-    auto map = [&](int r) { return r < 0 ? r : id[r]; };
-    for (Op op : p) {
-        if (op.code == OP_UPDATE) {
-            op.a = map(op.a);
-            op.b = map(op.b);
-            id[op.dst] = next++;
-            op.dst = id[op.dst];
-        } else {
-            op.a = map(op.a);
-            op.b = map(op.b);
-        }
-        ops.push_back(op);
-    }
-}
-
 // Register program of the lnL: Felsenstein's post-order pass rooted on edge
 // 0, written for a machine whose only partials are an accumulator and a
 // small stack.  Of an internal node's two child subtrees, the one needing
@@ -187,12 +167,20 @@ int compile_loglik_reg(const Tree &t, std::vector<Op> &ops) {
         for (int j = 0; j < 3; ++j)
             if (t.nbr[3 * v + j] != parent) { c[k] = t.nbr[3 * v + j]; e[k] = t.nedge[3 * v + j]; ++k; }
     };
+    // stack slots the side of node v away from parent needs, each computed once
+    std::vector<int> known(3 * (size_t)std::max(1, t.n_nodes), -1);
     std::function<int(int, int)> need = [&](int v, int parent) -> int {
         if (v < n) return 0;
-        int c[2], e[2];
-        child_pair(v, parent, c, e);
-        const int a = need(c[0], v), b = need(c[1], v);
-        return a == b ? a + 1 : std::max(a, b);
+        int j = 0;
+        while (t.nbr[3 * v + j] != parent) ++j;
+        int &k = known[3 * (size_t)v + j];
+        if (k < 0) {
+            int c[2], e[2];
+            child_pair(v, parent, c, e);
+            const int a = need(c[0], v), b = need(c[1], v);
+            k = a == b ? a + 1 : std::max(a, b);
+        }
+        return k;
     };
     int depth = 0;
     auto emit_op = [&](int code, int dst, int a, int ea, int b, int eb) {
@@ -240,8 +228,6 @@ int compile_loglik_reg(const Tree &t, std::vector<Op> &ops) {
         emit(v, u, 1);
         emit_op(OP_REVAL, 0, REF_STACK0, 0, REF_ACC, 0);
     }
-    // the kernel reads two ops ahead
-    for (int k = 0; k < kRegAhead; ++k) ops.push_back(Op(ops.back()));
     return depth;
 }
 

@@ -134,3 +134,23 @@ def test_scaled_partials(ctx, mean):
         got = pt.pt_batch_loglik(ctx, [A], pt.Trees([e]), b)
         want = oc.loglik(oc.Data(tips, w, RATES, FREQS, 0.3, K), e, b)
         close(got, np.array([want]), "scaled K %d mean %g lnL %.1f" % (K, mean, want), 1e-11)
+
+
+def test_optimised_lnl_of_the_deepest_tree(ctx):
+    """The lnL that an optimisation with FP32 partials reports comes from
+    k_prune at the final lengths, also beyond the eight stack slots that the
+    likelihood calls take: a balanced tree of 1024 taxa needs nine."""
+    rng = np.random.default_rng(700)
+    n, P = 1024, 21
+    e = balanced(n, rng)
+    b = rng.exponential(0.05, size=len(e))
+    tips = np.repeat((1 << rng.integers(0, 4, size=(1, P))).astype(np.uint8), n, 0)
+    change = rng.random((n, P)) < 0.2
+    tips[change] = (1 << rng.integers(0, 4, size=int(change.sum()))).astype(np.uint8)
+    A = pt.Alignment(ctx, tips, np.ones(P), np.ones(6), np.full(4, 0.25), 1.0, 1)
+    mask = np.zeros(len(e), np.uint8)
+    mask[[0, 5, 900]] = 1
+    lnl, out, passes, status = pt.pt_batch_optimize_branches(ctx, [A], pt.Trees([e]), b, mask, precision=pt.PT_FP32)
+    assert status[0] == 0 and np.all(out[mask == 0] == b[mask == 0]) and np.any(out != b)
+    want = oc.loglik(oc.Data(tips, np.ones(P), np.ones(6), np.full(4, 0.25), 1.0, 1), e, out)
+    close(lnl, np.array([want]), "1024 taxa, lnL %.2f" % want, 1e-11)
