@@ -42,7 +42,7 @@ def kernel_hash():
     """Hash of the sources that decide the optimiser's work per launch (its
     kernels and the host code that sets its programs and tolerances)."""
     h = hashlib.sha256()
-    for name in ("kernels.hip", "partials.hpp", "optimize.hpp", "lanes.hpp", "prune.hip", "abi.cpp", "tree.cpp"):
+    for name in ("kernels.hip", "partials.hpp", "optimize.hpp", "lanes.hpp", "prune.hip", "grad.hip", "abi.cpp", "tree.cpp"):
         with open(os.path.join(ROOT, "paper_1811_11007_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

@@ -236,10 +236,11 @@ pt_status pt_plan_optimize(pt_plan *plan, double *d_brlen_inout, const pt_opt *o
 pt_status pt_plan_grad(pt_plan *plan, const double *d_brlen, double *d_lnl,
                        double *d_grad, double *d_hess, void *stream);
 
-/* Patterns per tile of the stored post-order pass and the gradient (64, 128
- * or 256 = one block of that many threads, one pattern each; 256 by
- * default): more, smaller tiles give a small batch more blocks to spread
- * over the device, larger ones fewer passes over each tree's matrices.
+/* Patterns per tile of the stored post-order pass (64, 128 or 256 = one block
+ * of that many threads, one pattern each; 256 by default): more, smaller tiles
+ * give a small batch more blocks to spread over the device, larger ones fewer
+ * passes over each tree's matrices.  (The gradient has tiles of its own, on
+ * which the count has no effect.)
  * Re-tiling synchronises the device and drops the plan's captured graphs;
  * results are the same up to the order of the per-tile sums.  EINVAL for
  * another count.  pt_plan_autotune_tiles times the plan's gradient (or, with
@@ -254,14 +255,15 @@ pt_status pt_plan_autotune_tiles(pt_plan *plan, const double *d_brlen, int32_t *
 /* Which pass computes lnL on a PT_PLAN_LOGLIK plan.
  * PT_LOGLIK_REGISTERS (the default whenever every tree fits it): Felsenstein
  * pruning with no partial stored in device memory -- each pattern and
- * category keeps its partials in FP64, an accumulator in registers and a
- * stack of at most 8 slots in LDS, filled in an order that keeps it shallow
- * (enough for any tree of fewer than 512 taxa), and per pattern only the tip
- * codes and the weight are read; the result is FP64 in either precision.
- * A block needs 32 bytes per thread per stack slot plus the tile's tip codes
- * (n bytes per pattern) within the device's LDS per block.
- * PT_LOGLIK_STORED: the post-order pass that starts an optimisation or a
- * gradient, storing every partial in the plan's precision (with FP32
+ * category keeps its partials in FP64 registers, an accumulator and a stack
+ * of at most 8 slots, filled in an order that keeps it shallow (enough for
+ * any tree of fewer than 512 taxa), and per pattern only the tip codes and
+ * the weight are read; the result is FP64 in either precision.  A tree fits
+ * when n bytes per pattern of 256 patterns (512 with one padded category, 128
+ * with eight), plus, beyond four slots, 64 bytes per slot and lane, are within
+ * the device's LDS per block.
+ * PT_LOGLIK_STORED: the post-order pass that starts an optimisation,
+ * storing every partial in the plan's precision (with FP32
  * partials its lnL carries their rounding, about 1e-4 at a few thousand
  * sites).  PT_EUNSUPPORTED for PT_LOGLIK_REGISTERS when a tree does not fit;
  * such a plan uses the stored pass.  Gradient calls with FP32 partials

@@ -107,7 +107,7 @@ struct pt_plan {
     int n_trees = 0;
     int64_t n_edges = 0;
     int max_P = 0, max_E = 0, n_tiles = 0, kp = 1;
-    int tile_pats = pt::kTileBlock;      // patterns per tile of the stored pass and gradient
+    int tile_pats = pt::kTileBlock;      // patterns per tile of the stored pass
     size_t tile_cap = 0, part_cap = 0;   // allocated entries of d_tile_tree and d_part
     std::vector<int> tree_E;
     AlnDev *d_alns = nullptr;
@@ -121,6 +121,10 @@ struct pt_plan {
     TreeDev *d_trees_reg = nullptr;
     int32_t *d_tile_tree_reg = nullptr;
     double *d_part_reg = nullptr;
+    // the gradient's tiles and sums (k_grad)
+    int32_t *d_tile_tree_gr = nullptr;
+    double *d_part_gr = nullptr;
+    int n_tiles_gr = 0;
     int n_tiles_reg = 0, reg_depth = 0, reg_taxa = 0, reg_items = 0;
     void *d_clv = nullptr;
     uint16_t *d_cnt = nullptr;
@@ -423,13 +427,13 @@ pt_status configure_shape(pt_plan *pl, int block, int groups = 1) {
     return PT_OK;
 }
 
-// Re-tiles the stored pass and the gradient at `pats` patterns per tile:
+// Re-tiles the stored pass at `pats` patterns per tile:
 // each tree's tile count, the tiles of the longest programs first (as at
 // build time), the tile-to-tree map and the per-tile sums, reallocated when
 // they grow.  Captured graphs are dropped.
 pt_status set_tile_pats(pt_plan *pl, int pats) {
     if (!pt::tile_patterns_supported(pats)) return fail(PT_EINVAL, "patterns per tile must be 64, 128 or 256");
-    if (!(pl->kinds & (PT_PLAN_LOGLIK | PT_PLAN_GRAD)) || pl->n_trees == 0) {
+    if (!(pl->kinds & PT_PLAN_LOGLIK) || pl->n_trees == 0) {
         pl->tile_pats = pats;
         return PT_OK;
     }
@@ -438,16 +442,16 @@ pt_status set_tile_pats(pt_plan *pl, int pats) {
     for (int b = 0; b < B; ++b) order[b] = b;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return pl->tree_E[x] > pl->tree_E[y]; });
     std::vector<int32_t> tile_tree;
-    std::vector<TreeDev> tll = pl->tll_h, tgr = pl->tgr_h;
+    std::vector<TreeDev> tll = pl->tll_h;
     int tiles = 0;
     for (int b : order) {
         const int nt = (pl->alns_h[b].P + pats - 1) / pats;
-        tll[b].n_tiles = tgr[b].n_tiles = nt;
-        tll[b].tile_begin = tgr[b].tile_begin = tiles;
+        tll[b].n_tiles = nt;
+        tll[b].tile_begin = tiles;
         for (int x = 0; x < nt; ++x) tile_tree.push_back(b);
         tiles += nt;
     }
-    const size_t part = 3 * (size_t)tiles * std::max(1, pl->max_E);
+    const size_t part = (size_t)tiles;
     PT_HIP(hipSetDevice(pl->ctx->device));
     PT_HIP(hipDeviceSynchronize());  // no launch of this plan may still read the old tiles
     if ((size_t)tiles > pl->tile_cap) {
@@ -465,12 +469,8 @@ pt_status set_tile_pats(pt_plan *pl, int pats) {
         pl->part_cap = part;
     }
     PT_HIP(hipMemcpy(pl->d_tile_tree, tile_tree.data(), sizeof(int32_t) * tiles, hipMemcpyHostToDevice));
-    if (pl->kinds & PT_PLAN_LOGLIK)
-        PT_HIP(hipMemcpy(pl->d_trees_ll, tll.data(), sizeof(TreeDev) * B, hipMemcpyHostToDevice));
-    if (pl->kinds & PT_PLAN_GRAD)
-        PT_HIP(hipMemcpy(pl->d_trees_gr, tgr.data(), sizeof(TreeDev) * B, hipMemcpyHostToDevice));
+    PT_HIP(hipMemcpy(pl->d_trees_ll, tll.data(), sizeof(TreeDev) * B, hipMemcpyHostToDevice));
     pl->tll_h = tll;
-    pl->tgr_h = tgr;
     pl->n_tiles = tiles;
     pl->tile_pats = pats;
     for (auto &kv : pl->execs) (void)hipGraphExecDestroy(kv.second);
@@ -629,8 +629,11 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
         base.pm_off = pm_off;
         base.n_tiles = (int)((ad.P + tile_pats - 1) / tile_pats);
         base.tile_begin = 0;  // assigned below, longest programs first
-        clv_off += (int64_t)c.n_slots * kp * ad.P * 4;
-        cnt_off += (int64_t)c.n_slots * ad.P;
+        // the gradient keeps a slot per internal node; the stored pass and the
+        // optimisation one per node and neighbour, with scaler counts
+        const bool directional = kinds & (PT_PLAN_LOGLIK | PT_PLAN_OPTIMIZE);
+        clv_off += (int64_t)(directional ? c.n_slots : c.n_slots / 3) * kp * ad.P * 4;
+        cnt_off += directional ? (int64_t)c.n_slots * ad.P : 0;
         pm_off += (int64_t)E * kp * 16;
         for (int64_t i = 0; i < E; ++i) edge_tree[base.edge_off + i] = b;
         tll[b] = tgr[b] = top[b] = base;
@@ -670,7 +673,21 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
         }
         tile_tree_reg = tiles_by_xcd(order, treg);
     }
-    if (kinds & (PT_PLAN_LOGLIK | PT_PLAN_GRAD)) {
+    std::vector<int32_t> tile_tree_gr;
+    if (kinds & PT_PLAN_GRAD) {
+        // longest programs first, as below
+        const int pats = pt::grad_tile_patterns(kp);
+        std::vector<int> order(B);
+        std::iota(order.begin(), order.end(), 0);
+        std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return pl->tree_E[x] > pl->tree_E[y]; });
+        for (int b : order) {
+            tgr[b].n_tiles = (alns[trees->aln_index[b]]->P + pats - 1) / pats;
+            tgr[b].tile_begin = pl->n_tiles_gr;
+            pl->n_tiles_gr += tgr[b].n_tiles;
+            tile_tree_gr.insert(tile_tree_gr.end(), tgr[b].n_tiles, b);
+        }
+    }
+    if (kinds & PT_PLAN_LOGLIK) {
         // Tiles of the trees with the longest programs first: the hardware
         // dispatches blocks in index order, so long tiles start early and the
         // launch does not end on a tail of them.
@@ -678,7 +695,7 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
         for (int b = 0; b < B; ++b) order[b] = b;
         std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return pl->tree_E[x] > pl->tree_E[y]; });
         for (int b : order) {
-            tll[b].tile_begin = tgr[b].tile_begin = top[b].tile_begin = tiles;
+            tll[b].tile_begin = tiles;
             for (int x = 0; x < tll[b].n_tiles; ++x) tile_tree.push_back(b);
             tiles += tll[b].n_tiles;
         }
@@ -694,7 +711,8 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
 
     // arena cap
     int64_t need = clv_off * (int64_t)store_bytes(precision) + cnt_off * 2 + pm_off * 8 +
-                   (int64_t)ops.size() * sizeof(Op) + (int64_t)tiles * std::max(1, pl->max_E) * 24 +
+                   (int64_t)ops.size() * sizeof(Op) + (int64_t)tiles * 12 +
+                   (int64_t)pt::grad_part_doubles(pl->n_tiles_gr, pl->max_E) * 8 + (int64_t)pl->n_tiles_gr * 4 +
                    (int64_t)NE * 16 + (int64_t)B * 4 * sizeof(TreeDev) + (int64_t)pl->n_tiles_reg * 28;
     int64_t cap = arena_cap();
     if (cap > 0 && need > cap)
@@ -729,9 +747,16 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
     if (tiles) {
         if ((st = dev_alloc(pl.get(), &pl->d_tile_tree, sizeof(int32_t) * tiles))) return st;
         PT_HIP(hipMemcpy(pl->d_tile_tree, tile_tree.data(), sizeof(int32_t) * tiles, hipMemcpyHostToDevice));
-        if ((st = dev_alloc(pl.get(), &pl->d_part, sizeof(double) * 3 * (size_t)tiles * std::max(1, pl->max_E)))) return st;
+        if ((st = dev_alloc(pl.get(), &pl->d_part, sizeof(double) * (size_t)tiles))) return st;
         pl->tile_cap = (size_t)tiles;
-        pl->part_cap = 3 * (size_t)tiles * std::max(1, pl->max_E);
+        pl->part_cap = (size_t)tiles;
+    }
+    if (pl->n_tiles_gr) {
+        if ((st = dev_alloc(pl.get(), &pl->d_tile_tree_gr, sizeof(int32_t) * tile_tree_gr.size()))) return st;
+        PT_HIP(hipMemcpy(pl->d_tile_tree_gr, tile_tree_gr.data(), sizeof(int32_t) * tile_tree_gr.size(),
+                         hipMemcpyHostToDevice));
+        if ((st = dev_alloc(pl.get(), &pl->d_part_gr, sizeof(double) * pt::grad_part_doubles(pl->n_tiles_gr, pl->max_E))))
+            return st;
     }
     if (kinds & PT_PLAN_OPTIMIZE) {
         std::vector<int32_t> order(B);
@@ -781,7 +806,7 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
     return PT_OK;
 }
 
-pt::BatchArgs batch_args(const pt_plan *pl, const TreeDev *trees, int part_cols) {
+pt::BatchArgs batch_args(const pt_plan *pl, const TreeDev *trees) {
     pt::BatchArgs a{};
     a.trees = trees;
     a.alns = pl->d_alns;
@@ -797,14 +822,13 @@ pt::BatchArgs batch_args(const pt_plan *pl, const TreeDev *trees, int part_cols)
     a.n_trees = pl->n_trees;
     a.n_tiles = pl->n_tiles;
     a.n_edges = pl->n_edges;
-    a.part_cols = part_cols;
     a.kp = pl->kp;
     return a;
 }
 
 // The same for the register-resident lnL.
 pt::BatchArgs reg_args(const pt_plan *pl) {
-    pt::BatchArgs r = batch_args(pl, pl->d_trees_reg, 1);
+    pt::BatchArgs r = batch_args(pl, pl->d_trees_reg);
     r.tile_tree = pl->d_tile_tree_reg;
     r.tile_of = pl->d_tile_tree_reg + pl->n_tiles_reg;
     r.part = pl->d_part_reg;
@@ -822,12 +846,18 @@ pt_status enqueue(pt_plan *pl, int kind, const double *brlen_c, double *brlen, c
     if (kind == PT_PLAN_LOGLIK || kind == PT_PLAN_GRAD) {
         const bool g = kind == PT_PLAN_GRAD;
         const bool reg_ll = !g && pl->reg_ok && !pl->ll_stored;
-        pt::BatchArgs a = batch_args(pl, g ? pl->d_trees_gr : pl->d_trees_ll, g ? std::max(1, pl->max_E) : 1);
-        if (!reg_ll) {
+        if (g) {
+            pt::BatchArgs a = batch_args(pl, pl->d_trees_gr);
+            a.tile_tree = pl->d_tile_tree_gr;
+            a.part = pl->d_part_gr;
+            a.n_tiles = pl->n_tiles_gr;
+            if ((e = pt::launch_grad(pl->precision, a, brlen_c, pl->max_E, lnl, grad, hess, s)) != hipSuccess) goto bad;
+        } else if (!reg_ll) {
+            pt::BatchArgs a = batch_args(pl, pl->d_trees_ll);
             if ((e = pt::launch_pmat(a, brlen_c, s)) != hipSuccess) goto bad;
             if ((e = pt::launch_tiles(pl->precision, pl->kp, pl->tile_pats, a, brlen_c, pl->lds_tiles, s)) != hipSuccess)
                 goto bad;
-            if ((e = pt::launch_reduce(g, a, lnl, grad, hess, s)) != hipSuccess) goto bad;
+            if ((e = pt::launch_reduce(a, lnl, s)) != hipSuccess) goto bad;
         }
         // lnL with every partial in FP64 registers: the likelihood call
         // itself, and the lnL a gradient call with FP32 partials reports
@@ -841,7 +871,7 @@ pt_status enqueue(pt_plan *pl, int kind, const double *brlen_c, double *brlen, c
         return PT_OK;
     }
     {
-        pt::BatchArgs a = batch_args(pl, pl->d_trees_opt, 1);
+        pt::BatchArgs a = batch_args(pl, pl->d_trees_opt);
         a.tab = pl->d_tab;
         a.prof = pl->d_prof;
         a.groups = pl->opt_groups;
@@ -1296,7 +1326,6 @@ pt_status pt_batch_loglik_noalloc(pt_ctx *ctx, pt_aln *const *alns, int32_t n_al
     a.n_trees = B;
     a.n_tiles = tiles;
     a.n_edges = NE;
-    a.part_cols = 1;
     a.kp = kp;
     a.reg_depth = depth;
     a.reg_taxa = n_max;
@@ -1716,11 +1745,19 @@ pt_status pt_plan_traffic(const pt_plan *plan, int32_t kind, const int32_t *pass
         const AlnDev &a = plan->alns_h[tv[t].aln];
         const double slot = (double)a.P * a.K * 4 * b + (double)a.P * 2, tip = (double)a.P;
         auto side = [&](int ref) { return ref < 0 ? tip : slot; };
+        // the gradient's sides: tips, the accumulator, slots with no counts
+        const double gslot = (double)a.P * a.K * 4 * b;
+        auto gside = [&](int ref) { return ref >= 0 ? tip : ref == pt::REF_ACC ? 0.0 : gslot; };
         auto prog = [&](int o0, int no) {
             double s2 = 0.0;
             for (int o = 0; o < no; ++o) {
                 const Op &op = plan->ops_h[o0 + o];
-                if (op.code == pt::OP_UPDATE) s2 += side(op.a) + side(op.b) + slot;
+                if (kind == PT_PLAN_GRAD) {
+                    s2 += gside(op.a) + gside(op.b);
+                    if (op.code == pt::OP_GUP) s2 += gslot;
+                    else if (op.code == pt::OP_GROOT) s2 += 8.0 * a.P;
+                    else s2 += gside(op.dst) + (op.b < 0 ? gslot : 0.0);
+                } else if (op.code == pt::OP_UPDATE) s2 += side(op.a) + side(op.b) + slot;
                 else s2 += side(op.a) + side(op.b) + 8.0 * a.P;
             }
             return s2;

@@ -21,9 +21,11 @@
 // rerun is bit-identical.
 //
 // Kernels: k_pmat (transition matrices), k_tiles32 / k_tiles64 (a tree's
-// likelihood or gradient program over one pattern tile), k_reduce (tile sums
-// in order), k_optimize (the whole branch-length smoothing loop of a tree,
-// one block per tree or one tree split over several blocks).
+// stored post-order pass over one pattern tile), k_reduce (tile sums in
+// order); in optimize.hpp k_optimize (the whole branch-length smoothing loop
+// of a tree, one block per tree or one tree split over several blocks).  The
+// likelihood that stores nothing and the gradient are in prune.hip and
+// grad.hip.
 #include "partials.hpp"
 
 namespace pt {
@@ -129,9 +131,8 @@ __device__ inline void prefetch_pm(const double *pm, int ea, int eb, float4 *row
     }
 }
 
-// Pattern-tile kernels (k_tiles32 / k_tiles64 below): each block runs its tree's program over one tile of
-// BS * kTileItems patterns.  LOGLIK programs end in one EVAL (column 0);
-// GRAD programs EVAL every edge.  Output: part[tile][col] = (lnL, d1, d2).
+// Pattern-tile kernels (k_tiles32 / k_tiles64 below): each block runs its tree's LOGLIK program, which ends in one
+// EVAL, over one tile of BS * kTileItems patterns.  Output: part[tile] = lnL.
 template <typename T, int BS, int KP>
 __device__ inline void tiles_body(const BatchArgs &a, const double *brlen) {
     extern __shared__ double lds[];
@@ -218,17 +219,10 @@ __device__ inline void tiles_body(const BatchArgs &a, const double *brlen) {
             last_dst = op.dst;
             continue;
         }
-        // lnL is read from output column 0 only (the likelihood program's one
-        // edge, the gradient program's first edge)
         const Sums3 r = eval_edge<T, BS, KP>(v, op.a, op.b, base, kTileItems, brlen[td.edge_off + op.dst], red, wx,
-                                             parity, nullptr, op.ea == 0);
+                                             parity);
         parity = r.parity;
-        if (threadIdx.x == 0) {
-            double *out = a.part + ((size_t)tile * a.part_cols + op.ea) * 3;
-            out[0] = r.l0;
-            out[1] = r.l1;
-            out[2] = r.l2;
-        }
+        if (threadIdx.x == 0) a.part[tile] = r.l0;
     }
 }
 
@@ -247,32 +241,14 @@ __global__ void __launch_bounds__(BS) k_tiles64(const BatchArgs a, const double 
     tiles_body<double, BS, KP>(a, brlen);
 }
 
-// Sum the tile partials of every tree (LOGLIK) or every edge (GRAD) in
-// tile order.
-__global__ void k_reduce(const BatchArgs a, bool grad, double *lnl, double *gout, double *hout) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (!grad) {
-        if (i >= a.n_trees) return;
-        const TreeDev &td = a.trees[i];
-        double s = 0.0;
-        for (int t = 0; t < td.n_tiles; ++t) s += a.part[((size_t)(td.tile_begin + t) * a.part_cols) * 3];
-        lnl[i] = s;
-        return;
-    }
-    if (i >= a.n_edges) return;
-    const int b = a.edge_tree[i];
-    const TreeDev &td = a.trees[b];
-    const int e = (int)(i - td.edge_off);
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-    for (int t = 0; t < td.n_tiles; ++t) {
-        const double *pp = a.part + ((size_t)(td.tile_begin + t) * a.part_cols + e) * 3;
-        s0 += pp[0];
-        s1 += pp[1];
-        s2 += pp[2];
-    }
-    gout[i] = s1;
-    if (hout) hout[i] = s2;
-    if (e == 0 && lnl) lnl[b] = s0;
+// lnL of every tree from its tiles, in tile order.
+__global__ void k_reduce(const BatchArgs a, double *lnl) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= a.n_trees) return;
+    const TreeDev &td = a.trees[i];
+    double s = 0.0;
+    for (int t = 0; t < td.n_tiles; ++t) s += a.part[td.tile_begin + t];
+    lnl[i] = s;
 }
 
 // ------------------------------------------------------------- dispatch
@@ -351,11 +327,9 @@ hipError_t launch_tiles(int precision, int kp, int tile_pats, const BatchArgs &a
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_reduce(bool grad, const BatchArgs &a, double *lnl, double *gout, double *hout,
-                         hipStream_t s) {
-    const int64_t n = grad ? a.n_edges : a.n_trees;
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_reduce, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a, grad, lnl, gout, hout);
+hipError_t launch_reduce(const BatchArgs &a, double *lnl, hipStream_t s) {
+    if (a.n_trees <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_reduce, dim3((unsigned)((a.n_trees + 255) / 256)), dim3(256), 0, s, a, lnl);
     return hipGetLastError();
 }
 

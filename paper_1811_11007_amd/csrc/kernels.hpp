@@ -18,13 +18,12 @@ struct BatchArgs {
     void *clv;                  // float or double partials
     uint16_t *cnt;
     double *pmat;               // [sum_b E_b * Kp_b * 16]
-    double *part;               // tile partial sums [tile][part_cols][3]
+    double *part;               // tile partial sums
     void *tab;                  // optimisation: per-block eigenbasis tables when not in LDS
     int32_t *queue;             // optimisation work counter
     int32_t n_trees;
     int32_t n_tiles;
     int64_t n_edges;            // total flat edges
-    int32_t part_cols;
     int32_t kp;                 // padded category count of every layout in the batch
     long long *prof;            // optimisation: per-tree phase counters [n_trees][8], or null
     int32_t groups;             // optimisation: blocks per tree (1: one block per tree, work queue)
@@ -87,8 +86,14 @@ hipError_t launch_prune(const BatchArgs &a, int items, double *lnl, hipStream_t 
 // device (with that device current) and kept.
 constexpr size_t kNoAllocBytes = (size_t)64 << 20;
 hipError_t noalloc_workspace(int device, void **out);
-hipError_t launch_reduce(bool grad, const BatchArgs &a, double *lnl, double *grad_out,
-                         double *hess_out, hipStream_t s);
+hipError_t launch_reduce(const BatchArgs &a, double *lnl, hipStream_t s);
+// lnL and every edge derivative (k_grad; hess null: first derivatives only):
+// patterns per tile, doubles of a.part, the launch.  a.pmat takes the
+// exponentials, a.clv n - 2 slots per tree.
+int grad_tile_patterns(int kp);
+size_t grad_part_doubles(int tiles, int max_edges);
+hipError_t launch_grad(int precision, const BatchArgs &a, const double *brlen, int max_edges, double *lnl,
+                       double *grad, double *hess, hipStream_t s);
 // The optimisation kernel at one (precision, block size).
 struct OptimizeShape {
     int (*occupancy)(int kp, bool tab_lds, bool grouped, size_t lds);

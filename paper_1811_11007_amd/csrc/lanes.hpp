@@ -105,6 +105,53 @@ __device__ inline double row_ror(double v) {
     return __hiloint2double(hi, lo);
 }
 
+// A double from another lane of the row by a DPP permutation.
+template <int CTRL>
+__device__ inline double dpp_add(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
+// Row 0 of a value (its first 16 lanes) in every row, and row 1 in row 2 (and
+// row 0): halves and rows of a wave are exchanged between two copies.
+__device__ inline double row0(double v) {
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    uint32_t w[2] = {(uint32_t)__double2loint(v), (uint32_t)__double2hiint(v)};
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        u2 r = __builtin_amdgcn_permlane32_swap(w[x], w[x], false, false);
+        r = __builtin_amdgcn_permlane16_swap(r.x, r.x, false, false);
+        w[x] = r.x;
+    }
+    return __hiloint2double((int)w[1], (int)w[0]);
+}
+
+__device__ inline double row1(double v) {
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    uint32_t w[2] = {(uint32_t)__double2loint(v), (uint32_t)__double2hiint(v)};
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        // rows 0 and 1 in both halves, then the odd rows in both rows of a half
+        u2 r = __builtin_amdgcn_permlane32_swap(w[x], w[x], false, false);
+        r = __builtin_amdgcn_permlane16_swap(r.x, r.x, false, false);
+        w[x] = r.y;
+    }
+    return __hiloint2double((int)w[1], (int)w[0]);
+}
+
+// Rows 0 and 2 in both rows of their half.
+__device__ inline double even_rows(double v) {
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    uint32_t w[2] = {(uint32_t)__double2loint(v), (uint32_t)__double2hiint(v)};
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        const u2 r = __builtin_amdgcn_permlane16_swap(w[x], w[x], false, false);
+        w[x] = r.x;
+    }
+    return __hiloint2double((int)w[1], (int)w[0]);
+}
+
 __device__ inline double lane_value(double v, int lane) {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
                             __builtin_amdgcn_readlane(__double2loint(v), lane));
@@ -119,6 +166,14 @@ __device__ inline double wave_sum(double v) {
     v += dpp_shr<0x114>(v);
     v += dpp_shr<0x118>(v);
     return (lane_value(v, 15) + lane_value(v, 31)) + (lane_value(v, 47) + lane_value(v, 63));
+}
+
+// 1 / x from the hardware estimate plus two Newton-Raphson steps.
+__device__ inline double recip(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(r, fma(-x, r, 1.0), r);
+    r = fma(r, fma(-x, r, 1.0), r);
+    return r;
 }
 
 }  // namespace pt

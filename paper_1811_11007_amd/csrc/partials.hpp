@@ -143,14 +143,6 @@ __device__ inline double pm_entry_ex(const ModelS *md, const double *ex, int k, 
     return s;
 }
 
-// 1 / x from the hardware estimate plus two Newton-Raphson steps.
-__device__ inline double recip(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(r, fma(-x, r, 1.0), r);
-    r = fma(r, fma(-x, r, 1.0), r);
-    return r;
-}
-
 // Fixed-order block sum of three values; every thread receives the totals.
 // `red` holds two buffers used alternately, so back-to-back sums need one
 // barrier each.

@@ -28,6 +28,14 @@ enum : int32_t {
     OP_REVAL = 5,    // lnL across edge eb: pi . (side a * (P(eb) . side b)); ea = eb
 };
 
+// Gradient programs (see k_grad): sides as in register programs, a stack slot
+// being the slot of an internal node.
+enum : int32_t {
+    OP_GUP = 6,    // inner partial of the node in slot dst: sides a, b across ea, eb
+    OP_GROOT = 7,  // edge eb between sides a and b
+    OP_GDOWN = 8,  // node with outer partial dst across edge tip_a: children a, b across ea, eb
+};
+
 // Side references of register programs: a leaf's tip (>= 0), the
 // accumulator, or stack slot REF_STACK0 - ref.
 constexpr int32_t REF_ACC = -1;

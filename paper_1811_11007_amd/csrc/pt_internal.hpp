@@ -33,7 +33,9 @@ void compile_loglik(const Tree &t, std::vector<Op> &ops);
 // lnL as a register program (OP_RUPDATE / OP_REVAL, rooted on
 // edge 0); returns the stack slots it needs.
 int compile_loglik_reg(const Tree &t, std::vector<Op> &ops);
-// Every directional partial once, then EVAL on every edge (column = edge).
+// lnL and every edge derivative as a gradient program (OP_GUP / OP_GROOT /
+// OP_GDOWN): inner partials in post-order from edge 0's ends, then outer ones
+// in pre-order.
 void compile_grad(const Tree &t, std::vector<Op> &ops);
 // Smoothing passes over the masked edges in depth-first edge order: before
 // each edge step, exactly the partial updates whose inputs changed.  `first`

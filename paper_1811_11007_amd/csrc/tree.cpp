@@ -232,15 +232,49 @@ int compile_loglik_reg(const Tree &t, std::vector<Op> &ops) {
 }
 
 void compile_grad(const Tree &t, std::vector<Op> &ops) {
-    Slots s(t);
-    s.out = &ops;
-    for (int e = 0; e < t.n_edges; ++e) {
-        int u = t.ends[2 * e], v = t.ends[2 * e + 1];
-        int ra = s.ref(u, v), rb = s.ref(v, u);
-        s.ensure(ra);
-        s.ensure(rb);
-        ops.push_back(edge_op(OP_EVAL, e, ra, rb, e));
-    }
+    const int n = t.n;
+    auto stored = [&](int v) { return v < n ? v : REF_STACK0 - (v - n); };  // a node's side, from memory
+    auto emit = [&](int code, int dst, int a, int ea, int b, int eb, int up) {
+        Op op{};
+        op.code = code;
+        op.dst = dst;
+        op.a = a;
+        op.ea = ea;
+        op.b = b;
+        op.eb = eb;
+        op.tip_a = up;
+        ops.push_back(op);
+    };
+    auto children = [&](int v, int parent, int c[2], int e[2]) {
+        int k = 0;
+        for (int j = 0; j < 3; ++j)
+            if (t.nbr[3 * v + j] != parent) { c[k] = t.nbr[3 * v + j]; e[k] = t.nedge[3 * v + j]; ++k; }
+        if (c[0] < n) { std::swap(c[0], c[1]); std::swap(e[0], e[1]); }  // a leaf second
+    };
+    // Inner partials of v's side; the last node made is still in the accumulator.
+    std::function<void(int, int)> up = [&](int v, int parent) {
+        if (v < n) return;
+        int c[2], e[2];
+        children(v, parent, c, e);
+        up(c[0], v);
+        up(c[1], v);
+        const bool both = c[1] >= n;
+        emit(OP_GUP, v - n, both || c[0] < n ? stored(c[0]) : REF_ACC, e[0], both ? REF_ACC : c[1], e[1], 0);
+    };
+    // Derivatives of the edges below v, whose outer partial is side `src`.
+    std::function<void(int, int, int, int)> down = [&](int v, int parent, int ep, int src) {
+        int c[2], e[2];
+        children(v, parent, c, e);
+        emit(OP_GDOWN, src, stored(c[0]), e[0], stored(c[1]), e[1], ep);
+        if (c[0] >= n) down(c[0], v, e[0], REF_ACC);
+        if (c[1] >= n) down(c[1], v, e[1], stored(c[1]));
+    };
+    const int u = t.ends[0], v = t.ends[1];
+    up(u, v);
+    up(v, u);
+    emit(OP_GROOT, 0, u >= n && v < n ? REF_ACC : stored(u), 0, v < n ? v : REF_ACC, 0, 0);
+    if (v >= n) down(v, u, 0, stored(u));
+    if (u >= n) down(u, v, 0, stored(v));
 }
 
 void compile_optimize(const Tree &t, const uint8_t *mask, std::vector<Op> &first,
