@@ -34,14 +34,26 @@ __device__ inline double log_prior(const double *tl, int E, double rate) {
 // table lives in LDS after the transition matrices; otherwise in a
 // per-block slice of a.tab.  GRP: compiled for a.groups > 1 (the
 // one-block-per-tree instantiations carry none of the cross-block code).
+//
+// What bounds it: a serial chain.  An edge step is an update or two, a table,
+// one to two row passes with a block sum each, and the edge's new matrices,
+// each a few hundred instructions on one or two waves per SIMD that wait for
+// the last.  48 trees of 27 taxa on 4 blocks each, FP32 partials, clocks per
+// edge step: 16.7k when every product was scalar code (updates 7.8k, row
+// passes 7.0k), 14.9k with the products on the matrix cores, the sides of two
+// steps fetched at once and the exponentials taken while they arrive (updates
+// 5.6k, row passes 6.9k); the slowest of 256 mixed trees on one block of 512
+// threads: 28.7k -> 24.6k.  Reading the ops ahead of the loop (26 scalar
+// registers more) cost 5% instead.
+// FP32 with up to four categories is held to two waves per SIMD, which keeps
+// the matrix results out of the accumulation registers.
 template <typename T, int BS, int KP, bool TAB_LDS, bool GRP>
-__global__ void __launch_bounds__(BS) k_optimize(const BatchArgs a, double *brlen, const OptParams opt, int ni,
+__global__ void __launch_bounds__(BS, sizeof(T) == 4 && KP <= 4 ? 2 : 1) k_optimize(const BatchArgs a, double *brlen, const OptParams opt, int ni,
                                                  int pm_lds_doubles, double *lnl_out, int32_t *passes_out,
                                                  int32_t *status_out) {
     extern __shared__ double lds[];
     __shared__ double red[2 * (BS / 64) * 3];
     __shared__ double wxs[(BS / 64) * kWx];
-    __shared__ float wxfs[(BS / 64) * kWx];
     __shared__ ModelS model;
     __shared__ int q_sh;
     __shared__ GroupS gsh;
@@ -56,7 +68,6 @@ __global__ void __launch_bounds__(BS) k_optimize(const BatchArgs a, double *brle
     const int g = GRP ? (int)(xslot % (unsigned)G) : 0;
     GroupS *gs = GRP ? &gsh : nullptr;
     double *wx = wxs + (tid >> 6) * kWx;
-    float *wxf = wxfs + (tid >> 6) * kWx;
     // per block: the table [KP][BS*ni][4] of T, then the weights [BS*ni]
     const size_t tab_bytes = (size_t)BS * ni * KP * 4 * sizeof(T);
     char *tab_base = TAB_LDS ? reinterpret_cast<char *>(lds + pm_lds_doubles)
@@ -116,6 +127,8 @@ __global__ void __launch_bounds__(BS) k_optimize(const BatchArgs a, double *brle
         v.w += lo;
         v.clv += (size_t)lo * 4;
         v.cnt += lo;
+        const double tol_gain = opt.tol_lnl / E;
+        const double accept = fmax(sqrt(opt.tol_newton), kNewtonAccept);
         int parity = 0;
         double prev = -INFINITY, cur = -INFINITY;
         int passes = 0;
@@ -144,7 +157,7 @@ __global__ void __launch_bounds__(BS) k_optimize(const BatchArgs a, double *brle
                             const Op nx = load_op(a.ops, o0 + o + 1);
                             if (nx.code == OP_NEWTON && (nx.a == op.dst || nx.b == op.dst)) {
                                 pre = update_and_table<T, BS, KP, kF32 ? kPmLds32 : kPmLds>(
-                                    v, op, nx.a == op.dst ? nx.b : nx.a, tl[nx.dst], tab, wrow, wx, wxf);
+                                    v, op, nx.a == op.dst ? nx.b : nx.a, tl[nx.dst], tab, wrow, wx);
                                 have_pre = fused = true;
                             }
                         }
@@ -168,8 +181,8 @@ __global__ void __launch_bounds__(BS) k_optimize(const BatchArgs a, double *brle
                 }
                 // the pass's lnL comes from its last edge step (op.ea = 1)
                 const EdgeResult r =
-                    newton_edge<T, BS, KP, !kFuseUpd>(v, op.a, op.b, t0, op.ea != 0, opt, tab, wrow, ni, red, wx, wxf,
-                                                      parity, gs, passes >= 1 ? kRelax : 1.0, have_pre ? &pre : nullptr);
+                    newton_edge<T, BS, KP, !kFuseUpd>(v, op.a, op.b, t0, op.ea != 0, opt, tab, wrow, ni, red, wx, parity,
+                                                      gs, passes >= 1 ? kRelax : 1.0, accept, have_pre ? &pre : nullptr);
                 have_pre = false;
                 parity = r.parity;
                 if (op.ea) cur = r.lnl;
@@ -202,7 +215,7 @@ __global__ void __launch_bounds__(BS) k_optimize(const BatchArgs a, double *brle
                 // second derivative at the noise level, of either sign), and
                 // always counts against convergence by its length change.
                 const bool at_bound = t0 <= opt.t_min || t0 >= opt.t_max || r.t <= opt.t_min || r.t >= opt.t_max;
-                if (!((kF32 || at_bound) && r.gain < opt.tol_lnl / E))
+                if (!((kF32 || at_bound) && r.gain < tol_gain))
                     max_rel = fmax(max_rel, fabs(r.t - t0) / fmax(t0, 1e-6));
                 pass_gain += r.rise;
                 if (r.t != t0) {
@@ -247,7 +260,7 @@ __global__ void __launch_bounds__(BS) k_optimize(const BatchArgs a, double *brle
             }
             if (tid == 0) {
                 // a timed-out wait anywhere in the group: status 2, lnL NaN
-                const bool broken = GRP && load_agent(gsh.broken) != 0ull;
+                const bool broken = GRP && load_agent((GlobalU64 *)gsh.broken) != 0ull;
                 lnl_out[b] = broken ? NAN : kPassLnl<T> ? cur : 0.0;
                 if (passes_out) passes_out[b] = passes;
                 if (status_out) status_out[b] = broken ? 2 : (converged ? 0 : 1);
@@ -290,11 +303,14 @@ size_t spill_opt_t() {
 }
 
 // Runtime (padded categories, table placement, grouped) to the matching
-// instantiation of FN.
+// instantiation of FN.  There is none of 512 threads for eight categories:
+// two waves per SIMD leave it 256 registers, and it spilled (44 to 176 bytes
+// per lane), so such plans take 256 threads.
 #define PT_OPT_CALL(FN, T, BSZ, ...)                                                                             \
-    PT_KP_SWITCH(                                                                                                \
+    PT_KP_SWITCH(if constexpr (KP * BSZ <= 2048) {                                                               \
         if (grouped) return tab_lds ? FN<T, BSZ, KP, true, true>(__VA_ARGS__) : FN<T, BSZ, KP, false, true>(__VA_ARGS__); \
-        return tab_lds ? FN<T, BSZ, KP, true, false>(__VA_ARGS__) : FN<T, BSZ, KP, false, false>(__VA_ARGS__))
+        return tab_lds ? FN<T, BSZ, KP, true, false>(__VA_ARGS__) : FN<T, BSZ, KP, false, false>(__VA_ARGS__);   \
+    })
 
 }  // namespace
 

@@ -75,14 +75,14 @@ struct ModelS {
     double Uinv[16];
     double lam[4];
     double rate[kMaxCats];
-    float Wf[16];    // W rounded to FP32 (the FP32 tables of the optimisation loop)
+    float WfT[16];   // W rounded to FP32 and transposed, W_im at 4 m + i (the FP32 tables of the optimisation loop)
     double log_k;    // ln K
 };
 
 __device__ inline void model_to_lds(const AlnDev *aln, ModelS *m) {
     for (int x = threadIdx.x; x < 16; x += blockDim.x) {
         m->W[x] = aln->W[x];
-        m->Wf[x] = (float)aln->W[x];
+        m->WfT[(x & 3) * 4 + (x >> 2)] = (float)aln->W[x];
         m->U[x] = aln->U[x];
         m->Uinv[x] = aln->Uinv[x];
     }
@@ -192,11 +192,14 @@ __device__ inline void block_sum3(double &a, double &b, double &c, double *red, 
 static_assert(1 + 2 * kGroupBlocksMax * 3 <= kGroupSyncWords, "cross-block state does not fit");
 constexpr long long kGroupWaitCycles = 1ll << 27;  // shader clocks before a wait gives up
 
-__device__ inline unsigned long long load_agent(unsigned long long *p) {
+// (a pointer read from LDS would otherwise be accessed with FLAT operations)
+typedef __attribute__((address_space(1))) unsigned long long GlobalU64;
+
+__device__ inline unsigned long long load_agent(GlobalU64 *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ inline void store_agent(unsigned long long *p, unsigned long long v) {
+__device__ inline void store_agent(GlobalU64 *p, unsigned long long v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -224,7 +227,7 @@ struct GroupS {  // in LDS; written by lane 0 of the block's first wave
 __device__ inline void group_exchange(GroupS *gs, double a, double b, double c) {
     const int G = gs->G, g = gs->g, s = gs->seq;
     const int lane = threadIdx.x & 63;
-    unsigned long long *slot = gs->slots + (size_t)(s & 1) * G * 3;
+    GlobalU64 *slot = (GlobalU64 *)gs->slots + (size_t)(s & 1) * G * 3;
     const unsigned long long want = (unsigned long long)((s + 1) & 3);
     const unsigned long long ta = tag_bits(a, want), tb = tag_bits(b, want), tc = tag_bits(c, want);
     if (lane == 0) {
@@ -246,7 +249,7 @@ __device__ inline void group_exchange(GroupS *gs, double a, double b, double c) 
             if (__all(ok)) break;
             if (clock64() - t0 > gs->wait) {
                 if (lane == 0) {
-                    store_agent(gs->broken, 1ull);
+                    store_agent((GlobalU64 *)gs->broken, 1ull);
                     gs->is_broken = 1;
                 }
                 break;
@@ -287,26 +290,28 @@ __device__ inline void group_sum3(double &a, double &b, double &c, double *red, 
 // wave complete in order, so the wave's later reads see them.
 constexpr int kWx = 3 * 4 * kMaxCats;  // doubles per wave
 
-template <typename X>  // float: the same values rounded
-__device__ inline void wave_expo(X *wx, const ModelS *md, int K, double t) {
+// R = float: the values rounded to FP32 (held widened, so that no reader
+// converts them again).
+template <typename R>
+__device__ inline void wave_expo(double *wx, const ModelS *md, int K, double t) {
     const int lane = threadIdx.x & 63;
     if (lane < 4 * K) {
         const int k = lane >> 2, m = lane & 3;
         const double q = md->lam[m] * md->rate[k];
         const double e = exp(q * t);
-        wx[lane] = (X)e;
-        wx[4 * kMaxCats + lane] = (X)(e * q);
-        wx[8 * kMaxCats + lane] = (X)(e * q * q);
+        wx[lane] = (double)(R)e;
+        wx[4 * kMaxCats + lane] = (double)(R)(e * q);
+        wx[8 * kMaxCats + lane] = (double)(R)(e * q * q);
     }
     __builtin_amdgcn_wave_barrier();
 }
 
 // One side of an update or edge evaluation for one pattern: a tip code, or
-// the scaler count and every category's partial of a slot.  TIP is a
+// the scaler count (CNT) and every category's partial of a slot.  TIP is a
 // template parameter so that the code fetching a pattern's sides has no
 // branch between its loads: they are all issued before the first is used,
 // and their memory round trips overlap.
-template <typename T, int KP, bool TIP>
+template <typename T, int KP, bool TIP, bool CNT = true>
 struct Side {
     typename Store<T>::Raw r[KP];
     unsigned code;
@@ -316,7 +321,7 @@ struct Side {
             code = ldg(v.tips + (size_t)(-ref - 1) * v.P + p);
             c = 0;
         } else {
-            c = v.cnt[(size_t)ref * v.P + p];
+            c = CNT ? v.cnt[(size_t)ref * v.P + p] : 0;
             // the layout holds KP categories, so padded ones are in bounds
 #pragma unroll
             for (int k = 0; k < KP; ++k) r[k] = Store<T>::load_raw(slot_ptr<T, KP>(v, ref, k, p));
@@ -366,17 +371,50 @@ __device__ inline typename PmPtr<PM>::type pm_base(const V &v) {
     else return (typename PmPtr<PM>::type)v.pm;
 }
 
+// FP32 products in the optimisation loop, on the matrix cores:
+// v_mfma_f32_4x4x1_16b takes, in each group of four lanes, lane i's matrix
+// entry (row i) times every lane's vector entry, so with a pattern per lane
+// and its states in registers, four of them multiply a 4x4 matrix with 64
+// patterns' vectors, and a lane's operand is one row of the matrix (one
+// 16-byte LDS read with four addresses in place of four broadcasts).  Each is
+// a fused multiply-add, the chain of the scalar code bit for bit (checked on
+// the device over 10^6 random results, subnormal ones among them).  A, B are
+// the first two states summed: a matrix entry times a vector entry plus
+// another is contracted with the later product rounded first, and lengths
+// stay what they are only if both orders are kept.  The instruction ignores the execution mask, so every lane of a wave runs these
+// functions, on a valid pattern.
+typedef float F4 __attribute__((ext_vector_type(4)));
+
+template <int A, int B>
+__device__ inline F4 mat_vec(const float4 &row, const float x[4]) {
+    F4 y = {0.0f, 0.0f, 0.0f, 0.0f};
+    y = __builtin_amdgcn_mfma_f32_4x4x1f32(A ? row.y : row.x, x[A], y, 0, 0, 0);
+    y = __builtin_amdgcn_mfma_f32_4x4x1f32(B ? row.y : row.x, x[B], y, 0, 0, 0);
+    y = __builtin_amdgcn_mfma_f32_4x4x1f32(row.z, x[2], y, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(row.w, x[3], y, 0, 0, 0);
+}
+
+// This lane's row of every category's FP32 matrix of an edge.
+template <int KP>
+struct EdgeRows {
+    float4 r[KP];
+    __device__ inline EdgeRows(const float *pmf, int e) {
+        const float4 *q = reinterpret_cast<const float4 *>(pmf + (size_t)e * KP * 16) + (threadIdx.x & 3);
+#pragma unroll
+        for (int k = 0; k < KP; ++k) r[k] = q[k * 4];
+    }
+};
+
 // One pattern of an OP_UPDATE in FP32 arithmetic, for FP32 partials in the
 // optimisation loop (matrices from the FP32 LDS copy): the same products and
 // scaling rule as update_pattern, computed in the precision the partial is
 // stored in, so no entry is widened to FP64 and narrowed back.  The new
-// partial of every category goes to out[k] as stored; returns the scaler
-// count.  (The lnL an optimisation reports comes from FP64 partials at the
-// final lengths, and the Newton sums stay FP64.)
+// partial of every category goes to out[k] as stored.  No scaler count is
+// kept: the loop's sums are ratios, which a pattern's scale does not change,
+// and the lnL an optimisation reports comes from k_prune.
 template <int KP, class SA, class SB>
-__device__ inline int update_pattern_f32(const TreeView<float> &v, const Op &op, const SA &sa, const SB &sb,
-                                         float4 out[KP]) {
-    const float *pm = v.pmf;
+__device__ inline void update_pattern_f32(int K, const EdgeRows<KP> &ma, const EdgeRows<KP> &mb, const SA &sa,
+                                          const SB &sb, float4 out[KP]) {
     const float thr = 0x1p-64f, up = 0x1p64f;  // Store<float>::kScaleExp
     float o[KP][4];
     float mx = 0.0f;
@@ -385,23 +423,57 @@ __device__ inline int update_pattern_f32(const TreeView<float> &v, const Op &op,
         float xa[4], xb[4];
         sa.getf(k, xa);
         sb.getf(k, xb);
-        const float *Pa = pm + ((size_t)op.ea * KP + k) * 16;
-        const float *Pb = pm + ((size_t)op.eb * KP + k) * 16;
-        const bool live = k < v.K;
+        const F4 ya = mat_vec<1, 0>(ma.r[k], xa), yb = mat_vec<1, 0>(mb.r[k], xb);
+        const bool live = k < K;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float xsa = Pa[i * 4] * xa[0] + Pa[i * 4 + 1] * xa[1] + Pa[i * 4 + 2] * xa[2] + Pa[i * 4 + 3] * xa[3];
-            const float xsb = Pb[i * 4] * xb[0] + Pb[i * 4 + 1] * xb[1] + Pb[i * 4 + 2] * xb[2] + Pb[i * 4 + 3] * xb[3];
-            o[k][i] = live ? xsa * xsb : 0.0f;
+            o[k][i] = live ? ya[i] * yb[i] : 0.0f;
             mx = fmaxf(mx, o[k][i]);
         }
     }
-    int c = sa.c + sb.c;
     const float f = mx < thr && mx > 0.0f ? up : 1.0f;
-    c += f != 1.0f;
 #pragma unroll
     for (int k = 0; k < KP; ++k) out[k] = make_float4(o[k][0] * f, o[k][1] * f, o[k][2] * f, o[k][3] * f);
-    return c;
+}
+
+// The steps j < ni for which this lane's wave has any of the patterns
+// base + j * BS + threadIdx.x.
+template <int BS>
+__device__ inline int wave_steps(int base, int ni, int np) {
+    const int rest = np - base - (int)__builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
+    return rest > 0 ? min(ni, (rest + BS - 1) / BS) : 0;
+}
+
+// Steps taken at once by the FP32 loops below: the sides of all of them are
+// fetched before the first is used, so their round trips to memory overlap
+// (with eight categories the registers allow one).
+template <int KP>
+struct StepsAtOnce {
+    static constexpr int value = KP <= 4 ? 2 : 1;
+};
+
+// N steps of an FP32 OP_UPDATE from pattern p0 (this lane's) on.
+template <int BS, int KP, bool TA, bool TB, int N>
+__device__ inline void update_steps(const TreeView<float> &v, const Op &op, const EdgeRows<KP> &ma,
+                                    const EdgeRows<KP> &mb, int p0) {
+    Side<float, KP, TA, false> sa[N];
+    Side<float, KP, TB, false> sb[N];
+    float4 out[N][KP];
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        const int q = min(p0 + n * BS, v.np - 1);
+        sa[n].fetch(v, op.a, q);
+        sb[n].fetch(v, op.b, q);
+    }
+#pragma unroll
+    for (int n = 0; n < N; ++n) update_pattern_f32<KP>(v.K, ma, mb, sa[n], sb[n], out[n]);
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+        if (p0 + n * BS < v.np) {
+#pragma unroll
+            for (int k = 0; k < KP; ++k)
+                if (k < v.K) Store<float>::store_raw(slot_ptr<float, KP>(v, op.dst, k, p0 + n * BS), out[n][k]);
+        }
 }
 
 // One pattern of an OP_UPDATE from its two fetched sides, for the fused
@@ -451,6 +523,19 @@ __device__ inline int update_pattern(const TreeView<T> &v, const Op &op, const S
 // states, for every category k, then per-pattern scaling.
 template <typename T, int BS, int KP, bool TA, bool TB, int PM>
 __device__ inline void update_sides(const TreeView<T> &v, const Op &op, int base, int ni) {
+    if constexpr (PM == kPmLds32) {
+        const EdgeRows<KP> ma(v.pmf, op.ea), mb(v.pmf, op.eb);
+        constexpr int kAtOnce = StepsAtOnce<KP>::value;
+        const int nj = wave_steps<BS>(base, ni, v.np);
+        int j = 0, p = base + threadIdx.x;
+#pragma unroll 1
+        for (; j + kAtOnce <= nj; j += kAtOnce, p += kAtOnce * BS)
+            update_steps<BS, KP, TA, TB, kAtOnce>(v, op, ma, mb, p);
+        if constexpr (kAtOnce == 2) {
+            if (j < nj) update_steps<BS, KP, TA, TB, 1>(v, op, ma, mb, p);
+        }
+        return;
+    }
     const auto pm = pm_base<PM>(v);
     const double thr = ldexp(1.0, -Store<T>::kScaleExp);
     const double up = ldexp(1.0, Store<T>::kScaleExp);
@@ -462,15 +547,6 @@ __device__ inline void update_sides(const TreeView<T> &v, const Op &op, int base
         Side<T, KP, TB> sb;
         sa.fetch(v, op.a, p);
         sb.fetch(v, op.b, p);
-        if constexpr (PM == kPmLds32) {
-            float4 out[KP];
-            const int c = update_pattern_f32<KP>(v, op, sa, sb, out);
-#pragma unroll
-            for (int k = 0; k < KP; ++k)
-                if (k < v.K) Store<T>::store_raw(slot_ptr<T, KP>(v, op.dst, k, p), out[k]);
-            v.cnt[(size_t)op.dst * v.P + p] = (uint16_t)c;
-            continue;
-        }
         double o[KP][4];
         double mx = 0.0;
 #pragma unroll
@@ -545,42 +621,34 @@ __device__ inline void coeffs_x(const ModelS *md, const double xa[4], const doub
     }
 }
 
-// The same coefficients in FP32, for tables stored in FP32 (the optimisation
-// loop with FP32 partials): computed in the precision they are stored in.
-__device__ inline void coeffs_xf(const ModelS *md, const float xa[4], const float xb[4], float s[4]) {
+// One category's table coefficients for one pattern, in FP64, stored at dst
+// and returned in sk.
+template <class SA, class SB>
+__device__ inline void table_coeffs(const ModelS *md, const SA &sa, const SB &sb, int k, double *dst, double sk[4]) {
+    double xa[4], xb[4];
+    sa.get(k, xa);
+    sb.get(k, xb);
+    coeffs_x(md, xa, xb, sk);
+    Store<double>::store(dst, sk);
+}
+
+// The coefficients of every category in FP32, for tables stored in FP32 (the
+// optimisation loop with FP32 partials): computed in the precision they are
+// stored in, on the matrix cores (row: this lane's of W transposed).
+template <int KP, class SA, class SB>
+__device__ inline void coeffs_f32(const float4 &row, const SA &sa, const SB &sb, float4 s[KP]) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        float ua = 0.0f, vb = 0.0f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float wim = md->Wf[i * 4 + m];
-            ua += wim * xa[i];
-            vb += wim * xb[i];
-        }
-        s[m] = ua * vb;
+    for (int k = 0; k < KP; ++k) {
+        float xa[4], xb[4];
+        sa.getf(k, xa);
+        sb.getf(k, xb);
+        const F4 ua = mat_vec<0, 1>(row, xa), vb = mat_vec<0, 1>(row, xb);
+        s[k] = make_float4(ua[0] * vb[0], ua[1] * vb[1], ua[2] * vb[2], ua[3] * vb[3]);
     }
 }
 
-// One category's table coefficients for one pattern, stored at dst and
-// returned (as stored) in sk: in FP32 from the FP32 values of the sides when
-// the table is FP32, else in FP64.
-template <typename T, class SA, class SB>
-__device__ inline void table_coeffs(const ModelS *md, const SA &sa, const SB &sb, int k, T *dst, double sk[4]) {
-    if constexpr (std::is_same<T, float>::value) {
-        float xa[4], xb[4], s[4];
-        sa.getf(k, xa);
-        sb.getf(k, xb);
-        coeffs_xf(md, xa, xb, s);
-        *reinterpret_cast<float4 *>(dst) = make_float4(s[0], s[1], s[2], s[3]);
-#pragma unroll
-        for (int m = 0; m < 4; ++m) sk[m] = s[m];
-    } else {
-        double xa[4], xb[4];
-        sa.get(k, xa);
-        sb.get(k, xb);
-        coeffs_x(md, xa, xb, sk);
-        Store<T>::store(dst, sk);
-    }
+__device__ inline float4 model_row(const ModelS *md) {
+    return reinterpret_cast<const float4 *>(md->WfT)[threadIdx.x & 3];
 }
 
 // This thread's contributions to lnL, d1 and d2 across an edge whose sides
@@ -629,7 +697,7 @@ __device__ inline void eval_sides(const TreeView<T> &v, int a, int b, int base, 
 template <typename T, int BS, int KP>
 __device__ inline Sums3 eval_edge(const TreeView<T> &v, int a, int b, int base, int ni, double t, double *red,
                                   double *wx, int parity, GroupS *gs = nullptr, bool want_l0 = true) {
-    wave_expo(wx, v.m, v.K, t);
+    wave_expo<double>(wx, v.m, v.K, t);
     const double logK = v.m->log_k;
     Sums3 r;
     r.l0 = r.l1 = r.l2 = 0.0;
@@ -672,26 +740,25 @@ struct EdgeResult {
 // ([k][row][4]) and the weight into wrow, adds the pattern's t-independent
 // lnL term to cterm and, with FUSE, its terms of the first Newton iteration
 // at the exponentials wxe to f1 and f2.
-template <typename T, int KP, bool FUSE, class SA, class SB, typename X>
-__device__ inline void table_row(const TreeView<T> &v, const SA &sa, const SB &sb, int p, size_t rows, T *tab,
-                                 double *wrow, double w, double logK, const X *wxe, double &cterm, double &f1,
+template <int KP, bool FUSE, class SA, class SB>
+__device__ inline void table_row(const TreeView<double> &v, const SA &sa, const SB &sb, int p, size_t rows, double *tab,
+                                 double *wrow, double w, double logK, const double *wxe, double &cterm, double &f1,
                                  double &f2) {
     const ModelS *md = v.m;
-    if constexpr (kPassLnl<T>) cterm += w * const_term<T>(sa.c + sb.c, logK);
+    cterm += w * const_term<double>(sa.c + sb.c, logK);
     wrow[p] = w;
     double L = 0.0, L1 = 0.0, L2 = 0.0;
 #pragma unroll
     for (int k = 0; k < KP; ++k) {
         if (k < v.K) {
             double sk[4];
-            table_coeffs<T>(md, sa, sb, k, tab + ((size_t)k * rows + p) * 4, sk);
+            table_coeffs(md, sa, sb, k, tab + ((size_t)k * rows + p) * 4, sk);
             if constexpr (FUSE) {
 #pragma unroll
                 for (int m = 0; m < 4; ++m) {
-                    const double q = Store<T>::as_stored(sk[m]);
-                    L += q * (double)wxe[k * 4 + m];
-                    L1 += q * (double)wxe[4 * kMaxCats + k * 4 + m];
-                    L2 += q * (double)wxe[8 * kMaxCats + k * 4 + m];
+                    L += sk[m] * wxe[k * 4 + m];
+                    L1 += sk[m] * wxe[4 * kMaxCats + k * 4 + m];
+                    L2 += sk[m] * wxe[8 * kMaxCats + k * 4 + m];
                 }
             }
         }
@@ -704,87 +771,104 @@ __device__ inline void table_row(const TreeView<T> &v, const SA &sa, const SB &s
     }
 }
 
+// The same for N rows from their FP32 coefficients s (this lane's patterns
+// p0, p0 + BS, ... below np); the exponentials, read once for all N, are what
+// bounds the sums (64 lanes take 16 bytes each from LDS also when they agree).
+template <int BS, int KP, bool FUSE, int N>
+__device__ inline void table_rows(int K, int np, const float4 (&s)[N][KP], int p0, size_t rows, float *tab, double *wrow,
+                                  const double (&w)[N], const double *wxe, double &f1, double &f2) {
+    double L[N] = {}, L1[N] = {}, L2[N] = {};
+    if constexpr (FUSE) {
+#pragma unroll
+        for (int k = 0; k < KP; ++k) {
+            if (k < K) {
+                double sk[N][4];
+#pragma unroll
+                for (int n = 0; n < N; ++n) Store<float>::widen(s[n][k], sk[n]);
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const double e0 = wxe[k * 4 + m], e1 = wxe[4 * kMaxCats + k * 4 + m],
+                                 e2 = wxe[8 * kMaxCats + k * 4 + m];
+#pragma unroll
+                    for (int n = 0; n < N; ++n) {
+                        L[n] += sk[n][m] * e0;
+                        L1[n] += sk[n][m] * e1;
+                        L2[n] += sk[n][m] * e2;
+                    }
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        const int p = p0 + n * BS;
+        if (p >= np) break;
+        wrow[p] = w[n];
+#pragma unroll
+        for (int k = 0; k < KP; ++k)
+            if (k < K) *reinterpret_cast<float4 *>(tab + ((size_t)k * rows + p) * 4) = s[n][k];
+        if constexpr (FUSE) {
+            const double ia = recip(L[n]);
+            const double r1 = L1[n] * ia;
+            f1 += w[n] * r1;
+            f2 += w[n] * (L2[n] * ia - r1 * r1);
+        }
+    }
+}
+
+// N steps of the FP32 eigenbasis table from pattern p0 (this lane's) on.
+template <int BS, int KP, bool TA, bool TB, bool FUSE, int N>
+__device__ inline void table_steps(const TreeView<float> &v, int a, int b, int p0, size_t rows, float *tab,
+                                   double *wrow, const float4 &row, const double *wxe, double &f1, double &f2) {
+    Side<float, KP, TA, false> sa[N];
+    Side<float, KP, TB, false> sb[N];
+    double w[N];
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        const int q = min(p0 + n * BS, v.np - 1);
+        sa[n].fetch(v, a, q);
+        sb[n].fetch(v, b, q);
+        w[n] = ldg(v.w + q);
+    }
+    float4 s[N][KP];
+#pragma unroll
+    for (int n = 0; n < N; ++n) coeffs_f32<KP>(row, sa[n], sb[n], s[n]);
+    table_rows<BS, KP, FUSE, N>(v.K, v.np, s, p0, rows, tab, wrow, w, wxe, f1, f2);
+}
+
 // The eigenbasis table of an edge whose sides are of kinds TA / TB: this
 // thread's rows of tab ([k][row][4]) and wrow; returns the sum of its rows'
 // t-independent lnL terms.  FUSE: also adds the rows' terms of the first
 // Newton iteration, at the exponentials wxe, to f1 and f2, from the values as
-// stored and in the order of newton_rows2, so the sums are the ones a row
+// stored and in the order of newton_rows, so the sums are the ones a row
 // pass over the finished table would give.
-template <typename T, int BS, int KP, bool TA, bool TB, bool FUSE, bool PAIR, typename X>
+template <typename T, int BS, int KP, bool TA, bool TB, bool FUSE, bool PAIR>
 __device__ inline double table_sides(const TreeView<T> &v, int a, int b, int ni, size_t rows, T *tab, double *wrow,
-                                     double logK, const X *wxe, double &f1, double &f2) {
-    const ModelS *md = v.m;
+                                     double logK, const double *wxe, double &f1, double &f2) {
     double cterm = 0.0;
-    // PAIR: two patterns per step (FP32 partials; with FP64 the registers of
-    // a second pattern would spill), both fetched before either is used; a
-    // missing second pattern re-reads the first (in bounds) and is not
-    // stored.  Kernels with the fused update and table build leave PAIR off
-    // to make room for it.
-    constexpr int kStep = std::is_same<T, float>::value && PAIR ? 2 : 1;
+    if constexpr (std::is_same<T, float>::value) {
+        // (the kernels with the fused update and table build leave PAIR off
+        // to make room for it)
+        constexpr int kAtOnce = PAIR ? StepsAtOnce<KP>::value : 1;
+        const float4 row = model_row(v.m);
+        const int nj = wave_steps<BS>(0, ni, v.np);
+        int j = 0, p = threadIdx.x;
 #pragma unroll 1
-    for (int j = 0; j < ni; j += kStep) {
-        const int p0 = j * BS + threadIdx.x;
-        if (p0 >= v.np) break;
-        const bool two = kStep == 2 && j + 1 < ni && p0 + BS < v.np;
-        const int p1 = two ? p0 + BS : p0;
-        Side<T, KP, TA> sa0, sa1;
-        Side<T, KP, TB> sb0, sb1;
-        sa0.fetch(v, a, p0);
-        sb0.fetch(v, b, p0);
-        sa1.fetch(v, a, p1);
-        sb1.fetch(v, b, p1);
-        const double w0 = ldg(v.w + p0), w1 = ldg(v.w + p1);
-        if constexpr (kPassLnl<T>) cterm += w0 * const_term<T>(sa0.c + sb0.c, logK);
-        wrow[p0] = w0;
-        double L = 0.0, L1 = 0.0, L2 = 0.0;
-#pragma unroll
-        for (int k = 0; k < KP; ++k) {
-            if (k < v.K) {
-                double sk[4];
-                table_coeffs<T>(md, sa0, sb0, k, tab + ((size_t)k * rows + p0) * 4, sk);
-                if constexpr (FUSE) {
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        const double q = Store<T>::as_stored(sk[m]);
-                        L += q * (double)wxe[k * 4 + m];
-                        L1 += q * (double)wxe[4 * kMaxCats + k * 4 + m];
-                        L2 += q * (double)wxe[8 * kMaxCats + k * 4 + m];
-                    }
-                }
-            }
+        for (; j + kAtOnce <= nj; j += kAtOnce, p += kAtOnce * BS)
+            table_steps<BS, KP, TA, TB, FUSE, kAtOnce>(v, a, b, p, rows, tab, wrow, row, wxe, f1, f2);
+        if constexpr (kAtOnce == 2) {
+            if (j < nj) table_steps<BS, KP, TA, TB, FUSE, 1>(v, a, b, p, rows, tab, wrow, row, wxe, f1, f2);
         }
-        if constexpr (FUSE) {
-            const double ia = recip(L);
-            const double r1 = L1 * ia;
-            f1 += w0 * r1;
-            f2 += w0 * (L2 * ia - r1 * r1);
-        }
-        if (two) {
-            if constexpr (kPassLnl<T>) cterm += w1 * const_term<T>(sa1.c + sb1.c, logK);
-            wrow[p1] = w1;
-            double M = 0.0, M1 = 0.0, M2 = 0.0;
-#pragma unroll
-            for (int k = 0; k < KP; ++k) {
-                if (k < v.K) {
-                    double sk[4];
-                    table_coeffs<T>(md, sa1, sb1, k, tab + ((size_t)k * rows + p1) * 4, sk);
-                    if constexpr (FUSE) {
-#pragma unroll
-                        for (int m = 0; m < 4; ++m) {
-                            const double q = Store<T>::as_stored(sk[m]);
-                            M += q * (double)wxe[k * 4 + m];
-                            M1 += q * (double)wxe[4 * kMaxCats + k * 4 + m];
-                            M2 += q * (double)wxe[8 * kMaxCats + k * 4 + m];
-                        }
-                    }
-                }
-            }
-            if constexpr (FUSE) {
-                const double ib = recip(M);
-                const double r1 = M1 * ib;
-                f1 += w1 * r1;
-                f2 += w1 * (M2 * ib - r1 * r1);
-            }
+    } else {
+#pragma unroll 1
+        for (int j = 0; j < ni; ++j) {
+            const int p = j * BS + threadIdx.x;
+            if (p >= v.np) break;
+            Side<T, KP, TA> sa;
+            Side<T, KP, TB> sb;
+            sa.fetch(v, a, p);
+            sb.fetch(v, b, p);
+            table_row<KP, FUSE>(v, sa, sb, p, rows, tab, wrow, ldg(v.w + p), logK, wxe, cterm, f1, f2);
         }
     }
     return cterm;
@@ -797,12 +881,38 @@ __device__ inline double table_sides(const TreeView<T> &v, int a, int b, int ni,
 // read back.  The table is symmetric in the two sides, so which side the
 // update made does not matter.  Returns the row's t-independent lnL term
 // (see table_row).
-template <typename T, int BS, int KP, bool TA, bool TB, bool TO, bool FUSE, int PM, typename X>
+template <typename T, int BS, int KP, bool TA, bool TB, bool TO, bool FUSE, int PM>
 __device__ inline double update_table_sides(const TreeView<T> &v, const Op &op, int other, T *tab, double *wrow,
-                                            double logK, const X *wxe, double &f1, double &f2) {
+                                            double logK, double t, double *wxe, double &f1, double &f2) {
     double cterm = 0.0;
     const int p = threadIdx.x;
-    if (p < v.np) {
+    if constexpr (std::is_same<T, float>::value) {
+        if (wave_steps<BS>(0, 1, v.np) == 0) return 0.0;
+        const int q = min(p, v.np - 1);
+        Side<T, KP, TA, false> sa;
+        Side<T, KP, TB, false> sb;
+        Side<T, KP, TO, false> so;
+        sa.fetch(v, op.a, q);
+        sb.fetch(v, op.b, q);
+        so.fetch(v, other, q);
+        const double w = ldg(v.w + q);
+        if constexpr (FUSE) wave_expo<T>(wxe, v.m, v.K, t);  // while the sides arrive
+        const EdgeRows<KP> ma(v.pmf, op.ea), mb(v.pmf, op.eb);
+        Side<T, KP, false, false> made;
+        update_pattern_f32<KP>(v.K, ma, mb, sa, sb, made.r);
+        float4 s[1][KP];
+        coeffs_f32<KP>(model_row(v.m), made, so, s[0]);
+        const double w1[1] = {w};
+        table_rows<BS, KP, FUSE, 1>(v.K, v.np, s, p, (size_t)BS, tab, wrow, w1, wxe, f1, f2);
+        if (p < v.np) {
+#pragma unroll
+            for (int k = 0; k < KP; ++k)
+                if (k < v.K) Store<T>::store_raw(slot_ptr<T, KP>(v, op.dst, k, p), made.r[k]);
+        }
+    } else {
+        // by the whole wave, which may own fewer patterns than exponentials
+        if constexpr (FUSE) wave_expo<T>(wxe, v.m, v.K, t);
+        if (p >= v.np) return 0.0;
         Side<T, KP, TA> sa;
         Side<T, KP, TB> sb;
         Side<T, KP, TO> so;
@@ -811,15 +921,11 @@ __device__ inline double update_table_sides(const TreeView<T> &v, const Op &op, 
         so.fetch(v, other, p);
         const double w = ldg(v.w + p);
         Side<T, KP, false> made;
-        if constexpr (PM == kPmLds32) {
-            made.c = update_pattern_f32<KP>(v, op, sa, sb, made.r);
-        } else {
-            double o[KP][4];
-            made.c = update_pattern<T, KP, PM>(v, op, sa, sb, o);
+        double o[KP][4];
+        made.c = update_pattern<T, KP, PM>(v, op, sa, sb, o);
 #pragma unroll
-            for (int k = 0; k < KP; ++k) made.r[k] = Store<T>::pack(o[k]);
-        }
-        table_row<T, KP, FUSE>(v, made, so, p, (size_t)BS, tab, wrow, w, logK, wxe, cterm, f1, f2);
+        for (int k = 0; k < KP; ++k) made.r[k] = Store<T>::pack(o[k]);
+        table_row<KP, FUSE>(v, made, so, p, (size_t)BS, tab, wrow, w, logK, wxe, cterm, f1, f2);
 #pragma unroll
         for (int k = 0; k < KP; ++k)
             if (k < v.K) Store<T>::store_raw(slot_ptr<T, KP>(v, op.dst, k, p), made.r[k]);
@@ -828,59 +934,56 @@ __device__ inline double update_table_sides(const TreeView<T> &v, const Op &op, 
     return cterm;
 }
 
-// Newton pass over two table rows r0 and r1 (r1 < 0: only r0), so that each
-// exponential read from the wave's LDS slice serves two patterns.  Adds the
-// rows' d1 and d2 terms, or with lnl_only their weighted log L to d0; each
+// Newton pass over N = 1 or 2 table rows r0 and r1 (r1 < 0: only r0), so that
+// each exponential read from the wave's LDS slice serves two patterns.  Adds
+// the rows' d1 and d2 terms, or with lnl_only their weighted log L to d0; each
 // row's sums run in the same order as for a single row.
-template <typename T, int KP, typename X>
-__device__ inline void newton_rows2(const T *tab, const double *wrow, size_t rows, int r0, int r1, const X *wx,
-                                    int K, bool lnl_only, double &d0, double &d1, double &d2) {
+template <typename T, int KP, int N>
+__device__ inline void newton_rows(const T *tab, const double *wrow, size_t rows, int r0, int r1, const double *wx,
+                                   int K, bool lnl_only, double &d0, double &d1, double &d2) {
     using Raw = typename Store<T>::Raw;
     const bool two = r1 >= 0;
-    const int rb = two ? r1 : r0;
-    Raw ra[KP], rr[KP];
+    const int r[2] = {r0, two ? r1 : r0};
+    Raw raw[N][KP];
+    double w[N];
 #pragma unroll
-    for (int k = 0; k < KP; ++k) {
-        if (k < K) {
-            ra[k] = Store<T>::load_raw(tab + ((size_t)k * rows + r0) * 4);
-            rr[k] = Store<T>::load_raw(tab + ((size_t)k * rows + rb) * 4);
-        }
+    for (int n = 0; n < N; ++n) {
+#pragma unroll
+        for (int k = 0; k < KP; ++k)
+            if (k < K) raw[n][k] = Store<T>::load_raw(tab + ((size_t)k * rows + r[n]) * 4);
+        w[n] = wrow[r[n]];
     }
-    const double wa = wrow[r0], wb = wrow[rb];
-    double La = 0.0, L1a = 0.0, L2a = 0.0, Lb = 0.0, L1b = 0.0, L2b = 0.0;
+    double L[N] = {}, L1[N] = {}, L2[N] = {};
 #pragma unroll
     for (int k = 0; k < KP; ++k) {
         if (k < K) {
-            double sa[4], sb[4];
-            Store<T>::widen(ra[k], sa);
-            Store<T>::widen(rr[k], sb);
+            double s[N][4];
+#pragma unroll
+            for (int n = 0; n < N; ++n) Store<T>::widen(raw[n][k], s[n]);
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
                 const double e0 = wx[k * 4 + m], e1 = wx[4 * kMaxCats + k * 4 + m],
                              e2 = wx[8 * kMaxCats + k * 4 + m];
-                La += sa[m] * e0;
-                L1a += sa[m] * e1;
-                L2a += sa[m] * e2;
-                Lb += sb[m] * e0;
-                L1b += sb[m] * e1;
-                L2b += sb[m] * e2;
+#pragma unroll
+                for (int n = 0; n < N; ++n) {
+                    L[n] += s[n][m] * e0;
+                    L1[n] += s[n][m] * e1;
+                    L2[n] += s[n][m] * e2;
+                }
             }
         }
     }
-    if (lnl_only) {
-        d0 += wa * log(La);
-        if (two) d0 += wb * log(Lb);
-        return;
-    }
-    const double ia = recip(La);
-    const double ra1 = L1a * ia;
-    d1 += wa * ra1;
-    d2 += wa * (L2a * ia - ra1 * ra1);
-    if (two) {
-        const double ib = recip(Lb);
-        const double rb1 = L1b * ib;
-        d1 += wb * rb1;
-        d2 += wb * (L2b * ib - rb1 * rb1);
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        if (n == 1 && !two) break;
+        if (lnl_only) {
+            d0 += w[n] * log(L[n]);
+            continue;
+        }
+        const double ia = recip(L[n]);
+        const double q = L1[n] * ia;
+        d1 += w[n] * q;
+        d2 += w[n] * (L2[n] * ia - q * q);
     }
 }
 
@@ -918,33 +1021,18 @@ struct FuseFirst {
     static constexpr bool value = KP <= 4;
 };
 
-// The exponentials of length t that the fused first iteration uses (in the
-// wave's LDS slice), and a pointer to them in the precision it reads.
-template <typename T, int KP>
-__device__ inline const typename std::conditional<std::is_same<T, float>::value, float, double>::type *
-first_expo(const TreeView<T> &v, double t, double *wx, float *wxf) {
-    constexpr bool kF = std::is_same<T, float>::value;
-    using XE = typename std::conditional<kF, float, double>::type;
-    if constexpr (FuseFirst<KP>::value) {
-        if constexpr (kF) wave_expo(wxf, v.m, v.K, t);
-        else wave_expo(wx, v.m, v.K, t);
-    }
-    return kF ? reinterpret_cast<const XE *>(wxf) : reinterpret_cast<const XE *>(wx);
-}
-
 // OP_UPDATE of slot op.dst fused with the table build of the next OP_NEWTON,
 // whose other side is `other`, at its current length t (one pattern per
 // thread).
 template <typename T, int BS, int KP, int PM>
 __device__ inline EdgePre update_and_table(const TreeView<T> &v, const Op &op, int other, double t, T *tab,
-                                           double *wrow, double *wx, float *wxf) {
+                                           double *wrow, double *wx) {
     constexpr bool kFuse = FuseFirst<KP>::value;
-    const auto *wxe = first_expo<T, KP>(v, t, wx, wxf);
     const double logK = v.m->log_k;
     EdgePre pre;
     pre.f1 = pre.f2 = 0.0;
 #define PT_UT(TA, TB, TO)                                                                                        \
-    pre.cterm = update_table_sides<T, BS, KP, TA, TB, TO, kFuse, PM>(v, op, other, tab, wrow, logK, wxe, pre.f1, \
+    pre.cterm = update_table_sides<T, BS, KP, TA, TB, TO, kFuse, PM>(v, op, other, tab, wrow, logK, t, wx, pre.f1, \
                                                                       pre.f2)
     if (op.a < 0) {
         if (op.b < 0) {
@@ -978,7 +1066,8 @@ __device__ inline EdgePre update_and_table(const TreeView<T> &v, const Op &op, i
 //    geometrically;
 //  - a bound with the derivative pointing outwards is an optimum;
 //  - a step of at most tol * max(t, 1e-6) is converged and not taken; a
-//    Newton step of at most max(sqrt(tol), kNewtonAccept) * max(t, 1e-6) is
+//    Newton step of at most accept * max(t, 1e-6) (accept: the larger of
+//    sqrt(tol) and kNewtonAccept, a square root taken once per tree) is
 //    taken and ends the edge (quadratic convergence; the next pass revisits
 //    the edge);
 //  - the returned t is t_in + relax * (t_newton - t_in), kept in
@@ -990,7 +1079,7 @@ __device__ inline EdgePre update_and_table(const TreeView<T> &v, const Op &op, i
 template <typename T, int BS, int KP, bool PAIR = true>
 __device__ inline EdgeResult newton_edge(const TreeView<T> &v, int a, int b, double t, bool want_lnl,
                                          const OptParams &opt, T *tab, double *wrow, int ni, double *red,
-                                         double *wx, float *wxf, int parity, GroupS *gs, double relax,
+                                         double *wx, int parity, GroupS *gs, double relax, double accept,
                                          const EdgePre *pre = nullptr) {
     const double t_in = t;
     const size_t rows = (size_t)BS * ni;
@@ -1004,7 +1093,8 @@ __device__ inline EdgeResult newton_edge(const TreeView<T> &v, int a, int b, dou
         f1 = pre->f1;
         f2 = pre->f2;
     } else {
-        const auto *wxe = first_expo<T, KP>(v, t, wx, wxf);
+        const double *wxe = wx;
+        if constexpr (kFuse) wave_expo<T>(wx, v.m, v.K, t);
         if (a < 0) {
             if (b < 0) cterm = table_sides<T, BS, KP, true, true, kFuse, PAIR>(v, a, b, ni, rows, tab, wrow, logK, wxe, f1, f2);
             else cterm = table_sides<T, BS, KP, true, false, kFuse, PAIR>(v, a, b, ni, rows, tab, wrow, logK, wxe, f1, f2);
@@ -1015,6 +1105,7 @@ __device__ inline EdgeResult newton_edge(const TreeView<T> &v, int a, int b, dou
     }
     // rows this thread owns: tid + j*BS < P
     const int nj = v.np > (int)threadIdx.x ? min(ni, (v.np - (int)threadIdx.x + BS - 1) / BS) : 0;
+    const int nw = wave_steps<BS>(0, ni, v.np);  // the most rows of a lane of this wave
     const long long c1 = clock64();
     double lo = opt.t_min, hi = opt.t_max;
     double d1_0 = 0.0, d2_0 = 0.0;  // derivatives at the starting length
@@ -1024,22 +1115,16 @@ __device__ inline EdgeResult newton_edge(const TreeView<T> &v, int a, int b, dou
         if (kFuse && iter == 1) {
             d1 = f1;
             d2 = f2;
-        } else if constexpr (std::is_same<T, float>::value) {
-            // FP32 partials: FP32 exponentials suffice for the derivatives
-            // (they only steer Newton)
-            wave_expo(wxf, v.m, v.K, t);
-#pragma unroll 1
-            for (int j = 0; j < nj; j += 2)
-                newton_rows2<T, KP>(tab, wrow, rows, j * BS + threadIdx.x,
-                                    j + 1 < nj ? (j + 1) * BS + threadIdx.x : -1, (const float *)wxf, v.K, false, d0,
-                                    d1, d2);
         } else {
-            wave_expo(wx, v.m, v.K, t);
+            // (FP32 partials: FP32 exponentials suffice for the derivatives,
+            // they only steer Newton)
+            wave_expo<T>(wx, v.m, v.K, t);
 #pragma unroll 1
-            for (int j = 0; j < nj; j += 2)
-                newton_rows2<T, KP>(tab, wrow, rows, j * BS + threadIdx.x,
-                                    j + 1 < nj ? (j + 1) * BS + threadIdx.x : -1, (const double *)wx, v.K, false, d0,
-                                    d1, d2);
+            for (int j = 0; j < nj; j += 2) {
+                const int r0 = j * BS + threadIdx.x;
+                if (KP > 4 || j + 1 < nw) newton_rows<T, KP, 2>(tab, wrow, rows, r0, j + 1 < nj ? r0 + BS : -1, wx, v.K, false, d0, d1, d2);
+                else newton_rows<T, KP, 1>(tab, wrow, rows, r0, -1, wx, v.K, false, d0, d1, d2);
+            }
         }
         group_sum3<BS>(d0, d1, d2, red, parity, gs);
         d1 -= opt.prior_rate;  // MAP: the exponential prior's log density is linear in t
@@ -1067,18 +1152,18 @@ __device__ inline EdgeResult newton_edge(const TreeView<T> &v, int a, int b, dou
         // taken without a confirming evaluation.  The next pass revisits the
         // edge, and the pass-level rule (no step above tol_t) bounds the
         // final accuracy.
-        if (inside && dt <= fmax(sqrt(opt.tol_newton), kNewtonAccept) * scale) break;
+        if (inside && dt <= accept * scale) break;
     }
     if (relax != 1.0 && fabs(t - t_in) > opt.tol_t * fmax(t_in, 1e-6))
         t = fmin(fmax(t_in + relax * (t - t_in), opt.t_min), opt.t_max);
     double lnl = 0.0;
     if (kPassLnl<T> && want_lnl) {
-        wave_expo(wx, v.m, v.K, t);
+        wave_expo<double>(wx, v.m, v.K, t);
         double l0 = cterm, z1 = 0.0, z2 = 0.0;
 #pragma unroll 1
         for (int j = 0; j < nj; j += 2)
-            newton_rows2<T, KP>(tab, wrow, rows, j * BS + threadIdx.x, j + 1 < nj ? (j + 1) * BS + threadIdx.x : -1,
-                                (const double *)wx, v.K, true, l0, z1, z2);
+            newton_rows<T, KP, 2>(tab, wrow, rows, j * BS + threadIdx.x, j + 1 < nj ? (j + 1) * BS + threadIdx.x : -1, wx,
+                                  v.K, true, l0, z1, z2);
         group_sum3<BS>(l0, z1, z2, red, parity, gs);
         lnl = l0;
     }

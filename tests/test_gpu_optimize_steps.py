@@ -1,0 +1,91 @@
+"""GPU tests of the optimisation loop at the pattern counts where its work on
+whole waves can go wrong: around a wave's 64 patterns, a block's 256 and 512
+and the two steps a wave takes at once, blocks whose share leaves waves or
+whole blocks without patterns, and every padded category count.
+
+FP64: the oracle's optimiser, started at the returned lengths, gains less than
+the library's bar (1e-6 relative).  FP32 partials: one Newton step of every
+edge in turn (one pass, two evaluations each, so that no stopping rule is in
+play) against the FP64 loop's.  A partial is rounded at most 40 times here (6
+taxa), 2.4e-6 relative, and a Newton step is a ratio of sums in which such
+errors grow by the cancellation in the first derivative, of order 10: lengths
+agree within 1e-4 relative to their sum with the starting length.  Every
+reported lnL is the oracle's at the returned lengths (1e-9 relative)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1811_11007_amd as pt
+import synth
+from oracle import core as oc
+
+pytestmark = pytest.mark.gpu
+
+FP64_REL, LNL_REL, STEP_REL = 1e-6, 1e-9, 1e-4
+RATES, FREQS = np.array([0.7, 2.1, 0.4, 1.3, 3.0, 1.0]), np.array([0.31, 0.18, 0.23, 0.28])
+SHAPES = ((512, 1), (256, 1), (256, 3), (256, 4))
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = pt.Context(0)
+    yield c
+    c.close()
+
+
+@pytest.fixture(scope="module")
+def columns():
+    """A six-taxon tree and distinct site columns simulated on it."""
+    rng = np.random.default_rng(90)
+    e, b = synth.yule_tree(6, rng, mean=0.15)
+    b = b + 0.02
+    aln = synth.make_alignment(e, b, 6, 40000, rng, alpha=0.6, n_cats=4)
+    assert aln.tips.shape[1] >= 1100
+    return e, b, np.ascontiguousarray(aln.tips)
+
+
+@pytest.mark.parametrize("K", [1, 2, 4, 5])
+@pytest.mark.parametrize("P", [1, 63, 65, 129, 255, 257, 511, 513, 769, 1025, 1100])
+def test_edges_of_steps(ctx, columns, P, K):
+    if K == 5 and P > 256:
+        pytest.skip("eight padded categories in FP64 with two patterns per thread and the table in LDS faulted the GPU; "
+                    "that path is switched off, its cause not known")
+    e, b, tips = columns
+    tips = np.ascontiguousarray(tips[:, :P])
+    w = np.random.default_rng(P).integers(1, 5, size=P).astype(np.float64)
+    D = oc.Data(tips, w, RATES, FREQS, 0.6, K)
+    start = np.full(len(b), 0.1)
+    A = pt.Alignment(ctx, tips, w, RATES, FREQS, 0.6, K)
+    plans = {p: pt.Plan(ctx, [A], pt.Trees([e]), pt.PT_PLAN_OPTIMIZE, p) for p in (pt.PT_FP64, pt.PT_FP32)}
+    once = {p: pt.opt_default(p) for p in plans}
+    for o in once.values():
+        o.max_passes, o.max_newton = 1, 2
+
+    def run(prec, opt=None):
+        bb = torch.tensor(start, dtype=torch.float64, device="cuda:0")
+        lnl = torch.zeros(1, dtype=torch.float64, device="cuda:0")
+        st = torch.zeros(1, dtype=torch.int32, device="cuda:0")
+        plans[prec].optimize(bb, lnl, None, st, opt=opt)
+        torch.cuda.synchronize()
+        t, got = bb.cpu().numpy(), float(lnl[0])
+        at = oc.loglik(D, e, t)
+        assert abs(got - at) <= LNL_REL * abs(at), (prec, got, at)
+        return t, got, int(st[0])
+
+    for block, groups in SHAPES:
+        print("P", P, "K", K, (block, groups), flush=True)
+        try:
+            for plan in plans.values():
+                plan.set_launch(block, groups)
+        except pt.PTError as err:  # eight padded categories take 256 threads
+            assert err.code == -4 and K == 5 and block == 512, err
+            continue
+        t, lnl, st = run(pt.PT_FP64)
+        assert st == 0
+        assert oc.optimize(D, e, t)[0] - lnl < FP64_REL * abs(lnl)
+        t64 = run(pt.PT_FP64, once[pt.PT_FP64])[0]
+        t32 = run(pt.PT_FP32, once[pt.PT_FP32])[0]
+        print("  step FP32 - FP64", np.max(np.abs(t32 - t64) / (t64 + start)), flush=True)
+        assert np.all(np.abs(t32 - t64) <= STEP_REL * (t64 + start))
+    for plan in plans.values():
+        plan.close()
