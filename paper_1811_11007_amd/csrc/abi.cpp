@@ -1894,7 +1894,7 @@ struct pt_mlp {
     float *d_p = nullptr, *d_m = nullptr, *d_v = nullptr, *d_g = nullptr;
     int cap = 0;
     float *d_h = nullptr, *d_y = nullptr, *d_dy = nullptr, *d_dz = nullptr;
-    double *d_rl = nullptr, *d_part = nullptr;  // d_part: row-tile sums of the weight gradient
+    double *d_rl = nullptr, *d_part = nullptr;  // d_part: the row blocks' sums of a gradient
 };
 
 namespace {
@@ -1908,19 +1908,31 @@ void mlp_free_scratch(pt_mlp *m) {
     m->cap = 0;
 }
 
+// What a pass needs in memory: of a network that fits in LDS, the blocks' sums
+// of a gradient (and the activations, where outputs overlap the inputs and
+// the layers run one after the other).
 pt_status mlp_scratch(pt_mlp *m, int rows) {
     if (rows <= m->cap) return PT_OK;
     mlp_free_scratch(m);
     const size_t r = (size_t)rows;
     PT_HIP(hipMalloc(&m->d_h, sizeof(float) * r * m->nh));
-    PT_HIP(hipMalloc(&m->d_dz, sizeof(float) * r * m->nh));
-    PT_HIP(hipMalloc(&m->d_y, sizeof(float) * r * m->no));
-    PT_HIP(hipMalloc(&m->d_dy, sizeof(float) * r * m->no));
-    PT_HIP(hipMalloc(&m->d_rl, sizeof(double) * r));
-    const size_t part = pt::mlp_wgrad_part_doubles(rows, m->ni, m->nh, m->no);
-    if (part) PT_HIP(hipMalloc(&m->d_part, sizeof(double) * part));
+    if (pt::mlp_rows_fit(m->ni, m->nh, m->no)) {
+        PT_HIP(hipMalloc(&m->d_part, sizeof(double) * pt::mlp_rows_part_doubles(rows, m->ni, m->nh, m->no)));
+    } else {
+        PT_HIP(hipMalloc(&m->d_dz, sizeof(float) * r * m->nh));
+        PT_HIP(hipMalloc(&m->d_y, sizeof(float) * r * m->no));
+        PT_HIP(hipMalloc(&m->d_dy, sizeof(float) * r * m->no));
+        PT_HIP(hipMalloc(&m->d_rl, sizeof(double) * r));
+        const size_t part = pt::mlp_wgrad_part_doubles(rows, m->ni, m->nh, m->no);
+        if (part) PT_HIP(hipMalloc(&m->d_part, sizeof(double) * part));
+    }
     m->cap = rows;
     return PT_OK;
+}
+
+// Whether two arrays of a and b bytes share any.
+bool overlap(const void *x, size_t a, const void *y, size_t b) {
+    return (uintptr_t)x < (uintptr_t)y + b && (uintptr_t)y < (uintptr_t)x + a;
 }
 
 }  // namespace
@@ -1977,9 +1989,16 @@ pt_status pt_mlp_set_params(pt_mlp *mlp, const float *params) {
 
 pt_status pt_mlp_forward(pt_mlp *mlp, const float *d_x, int32_t rows, float *d_y, void *stream) {
     if (!mlp || rows < 0 || (rows > 0 && (!d_x || !d_y))) return fail(PT_EINVAL, "bad arguments");
+    hipStream_t s = (hipStream_t)stream;
+    const int ni = mlp->ni, nh = mlp->nh, no = mlp->no;
+    if (pt::mlp_rows_fit(ni, nh, no) &&
+        !overlap(d_x, sizeof(float) * (size_t)rows * ni, d_y, sizeof(float) * (size_t)rows * no)) {
+        PT_HIP(pt::mlp_rows(d_x, mlp->d_p, rows, ni, nh, no, d_y, nullptr, nullptr, 0.0, 0.0, 0.0, nullptr, s));
+        return PT_OK;
+    }
     pt_status st = mlp_scratch(mlp, rows);
     if (st) return st;
-    PT_HIP(pt::mlp_forward(d_x, mlp->d_p, rows, mlp->ni, mlp->nh, mlp->no, mlp->d_h, d_y, (hipStream_t)stream));
+    PT_HIP(pt::mlp_forward(d_x, mlp->d_p, rows, ni, nh, no, mlp->d_h, d_y, s));
     return PT_OK;
 }
 
@@ -1989,9 +2008,14 @@ pt_status pt_mlp_warm_start(pt_mlp *mlp, const float *d_x, int32_t rows, const i
         return fail(PT_EINVAL, "bad arguments");
     if (!(t_min > 0.0) || !(t_max > t_min)) return fail(PT_EINVAL, "need 0 < t_min < t_max");
     if (!(shift > 0.0) || !std::isfinite(shift)) return fail(PT_EINVAL, "need shift > 0");
+    hipStream_t s = (hipStream_t)stream;
+    if (pt::mlp_rows_fit(mlp->ni, mlp->nh, mlp->no)) {
+        PT_HIP(pt::mlp_rows(d_x, mlp->d_p, rows, mlp->ni, mlp->nh, mlp->no, nullptr, d_pos, d_base, shift, t_min, t_max,
+                            d_brlen, s));
+        return PT_OK;
+    }
     pt_status st = mlp_scratch(mlp, rows);
     if (st) return st;
-    hipStream_t s = (hipStream_t)stream;
     PT_HIP(pt::mlp_forward(d_x, mlp->d_p, rows, mlp->ni, mlp->nh, mlp->no, mlp->d_h, mlp->d_y, s));
     PT_HIP(pt::mlp_warm_apply(mlp->d_y, d_pos, d_base, rows, mlp->no, shift, t_min, t_max, d_brlen, s));
     return PT_OK;
@@ -2003,6 +2027,11 @@ pt_status pt_mlp_gradient(pt_mlp *mlp, const float *d_x, const float *d_target, 
     pt_status st = mlp_scratch(mlp, rows);
     if (st) return st;
     hipStream_t s = (hipStream_t)stream;
+    if (pt::mlp_rows_fit(mlp->ni, mlp->nh, mlp->no)) {
+        PT_HIP(pt::mlp_rows_gradient(d_x, mlp->d_p, d_target, rows, mlp->ni, mlp->nh, mlp->no, mlp->d_part, d_grad,
+                                     d_loss, s));
+        return PT_OK;
+    }
     PT_HIP(pt::mlp_forward(d_x, mlp->d_p, rows, mlp->ni, mlp->nh, mlp->no, mlp->d_h, mlp->d_y, s));
     PT_HIP(pt::mlp_loss_grad(mlp->d_y, d_target, rows, mlp->no, mlp->d_dy, mlp->d_rl, d_loss, s));
     PT_HIP(pt::mlp_backward(d_x, mlp->d_p, mlp->d_h, mlp->d_dy, rows, mlp->ni, mlp->nh, mlp->no, mlp->d_dz, d_grad,

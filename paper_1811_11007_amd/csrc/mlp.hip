@@ -6,15 +6,16 @@
 //
 // Parameters live in one FP32 array packed as W1, b1, W2, b2 (row-major).
 // Training minimises the mean over rows and outputs of (y - target)^2 with
-// Adam.  Weight gradients are sums over rows, formed in a fixed order, so
-// training is deterministic: blocks of 32 rows staged in LDS, each block's
-// sums in FP64 and the blocks added in order (a network whose
-// staging exceeds 48 KiB of LDS: one block per parameter, per-thread strided
-// partial sums in FP64, then a fixed tree).  Matrices are small (n_in ~ 16,
-// n_hidden 128, n_out 5): the hidden layer is one thread per element with
-// the weights read through the cache; the output layer stages 64 rows of
-// activations and the weights in LDS; per-row activations are kept for the
-// backward pass.
+// Adam.  Weight gradients are sums over rows, formed in FP64 in a fixed order,
+// so training is deterministic.
+//
+// A network whose parameters and row tile fit in LDS (k_mlp_rows; the
+// warm-start one, 14-128-5, takes 24 to 34 KB) runs each row's whole pass in
+// one block: forward, start lengths, or forward and backward with the block's
+// sums of every gradient, which k_mlp_sum adds over the blocks.  Larger
+// networks take a kernel per step, with the activations in memory: the hidden
+// layer is one thread per element, the output layer and the weight gradients
+// stage 64 and 32 rows in LDS where that takes at most 48 KiB.
 #include <hip/hip_runtime.h>
 
 #include "mlp.hpp"
@@ -210,6 +211,194 @@ __global__ void k_mlp_wgrad_sum(const double *part, int tiles, int np, float *gr
     grad[q] = (float)s;
 }
 
+// The whole pass of kRows rows per block (256 threads): parameters and rows
+// are staged in LDS at once, a wave computes the hidden units of four rows
+// with a lane per unit, outputs are a thread each.  Every hidden unit and
+// output is summed in the order of k_mlp_hidden and k_mlp_out.
+//   y:     outputs, or null
+//   brlen: the warm start of k_warm_apply, or null
+//   GRAD:  the block's terms of every parameter's gradient, summed over its
+//          rows in order in FP64, and its sum of squared errors (entry np),
+//          to part[block][np + 1]
+// What bounds it: latencies.  A block is one wave per SIMD, and its output
+// sums are chains of nh fused multiply-adds.  16 rows per block give every
+// compute unit one block at 4096 rows; 4 rows per block were no faster at 1024
+// (7.8 us either way).  Measured with the 14-128-5 network: start lengths of
+// 1024 rows 18.0 -> 7.7 us (three kernels before), gradient of 4096 rows
+// 55.4 -> 18.7 us (eight before; of it k_mlp_rows 14.5, k_mlp_sum 3.6).
+constexpr int kRows = 16;
+
+struct RowsLds {  // offsets in floats; the FP64 arrays come first
+    int ld, nip, nop;
+    int x64, e64, l64, par, x, h, z, total;
+    __host__ __device__ RowsLds(int ni, int nh, int no, bool grad) {
+        ld = nh + 1;  // rows padded by one word: lanes of several rows read different banks
+        nip = (ni + 7) & ~7;
+        nop = (no + 7) & ~7;
+        int o = 0;
+        x64 = o; o += grad ? 2 * kRows * nip : 0;
+        e64 = o; o += grad ? 2 * kRows * nop : 0;
+        l64 = o; o += grad ? 2 * kRows * no : 0;
+        par = o; o += ni * nh + nh + nh * no + no;
+        x = o; o += kRows * ni;
+        h = o; o += kRows * ld;
+        z = o; o += grad ? kRows * ld : 0;
+        total = o;
+    }
+};
+
+struct WarmArgs {
+    const int32_t *pos;
+    const double *base;
+    double shift, t_min, t_max;
+    double *brlen;
+};
+
+__device__ inline void warm_apply(const WarmArgs &a, int64_t g, float y) {
+    const int32_t at = a.pos[g];
+    if (at < 0) return;
+    const double v = (fmax(a.base[g], 0.0) + a.shift) * exp((double)y) - a.shift;
+    a.brlen[at] = fmin(fmax(v, a.t_min), a.t_max);
+}
+
+template <bool GRAD>
+__global__ void __launch_bounds__(256) k_mlp_rows(const float *x, const float *p, int rows, int ni, int nh, int no,
+                                                   float *y, const WarmArgs warm, const float *target,
+                                                   double *part) {
+    extern __shared__ double lds64[];
+    float *lds = reinterpret_cast<float *>(lds64);
+    const RowsLds at(ni, nh, no, GRAD);
+    double *x64 = lds64 + at.x64 / 2, *e64 = lds64 + at.e64 / 2, *l64 = lds64 + at.l64 / 2;
+    float *W1 = lds + at.par, *b1 = W1 + ni * nh, *W2 = b1 + nh, *b2 = W2 + nh * no;
+    float *tx = lds + at.x, *th = lds + at.h, *tz = lds + at.z;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int np = ni * nh + nh + nh * no + no;
+    const int r0 = blockIdx.x * kRows;
+    const int nr = min(kRows, rows - r0);
+    for (int i = tid; i < nr * ni; i += 256) tx[i] = x[(size_t)r0 * ni + i];
+#pragma unroll 12
+    for (int i = tid; i < np; i += 256) W1[i] = p[i];
+    if constexpr (GRAD) {
+        for (int i = tid; i < kRows * at.nip; i += 256) {
+            const int r = i / at.nip, f = i % at.nip;
+            x64[i] = r < nr && f < ni ? (double)x[(size_t)(r0 + r) * ni + f] : 0.0;
+        }
+        for (int i = tid; i < kRows * at.nop; i += 256) e64[i] = 0.0;
+    }
+    __syncthreads();
+    constexpr int kPerWave = kRows / 4;
+    const int rw = wave * kPerWave;
+    for (int h = lane; h < nh; h += 64) {
+        float z[kPerWave];
+#pragma unroll
+        for (int u = 0; u < kPerWave; ++u) z[u] = b1[h];
+        // (a tile's missing rows read what LDS holds there and are not kept)
+#pragma unroll 7
+        for (int f = 0; f < ni; ++f) {
+            const float w = W1[f * nh + h];
+#pragma unroll
+            for (int u = 0; u < kPerWave; ++u) z[u] += tx[(rw + u) * ni + f] * w;
+        }
+#pragma unroll
+        for (int u = 0; u < kPerWave; ++u) th[(rw + u) * at.ld + h] = rw + u < nr ? tanhf(z[u]) : 0.0f;
+    }
+    __syncthreads();
+    const float scale = 2.0f / ((float)rows * (float)no);
+    for (int g = tid; g < nr * no; g += 256) {
+        const int r = g / no, o = g % no;
+        float s = b2[o];
+#pragma unroll 16
+        for (int h = 0; h < nh; ++h) s += th[r * at.ld + h] * W2[h * no + o];
+        const size_t out = (size_t)r0 * no + g;
+        if constexpr (GRAD) {
+            const float d = s - target[out];
+            e64[r * at.nop + o] = (double)(d * scale);
+            l64[g] = (double)d * d;
+        } else {
+            if (y) y[out] = s;
+            if (warm.brlen) warm_apply(warm, (int64_t)out, s);
+        }
+    }
+    if constexpr (GRAD) {
+        __syncthreads();
+        for (int h = lane; h < nh; h += 64) {
+            // (zero for a missing row, whose e64 is zero)
+            float s[kPerWave] = {};
+#pragma unroll 5
+            for (int o = 0; o < no; ++o) {
+                const float w = W2[h * no + o];
+#pragma unroll
+                for (int u = 0; u < kPerWave; ++u) s[u] += (float)e64[(rw + u) * at.nop + o] * w;
+            }
+#pragma unroll
+            for (int u = 0; u < kPerWave; ++u) {
+                const float a = th[(rw + u) * at.ld + h];
+                tz[(rw + u) * at.ld + h] = s[u] * (1.0f - a * a);
+            }
+        }
+        __syncthreads();
+        // a unit of work is one hidden unit and eight inputs (x dz), or eight
+        // outputs (h dy); the unit of the first inputs also has b1
+        double *out = part + (size_t)blockIdx.x * (np + 1);
+        const int cf = at.nip / 8, units = (cf + at.nop / 8) * nh;
+        for (int q = tid; q < units; q += 256) {
+            const int c = q / nh, h = q % nh;
+            const bool in = c < cf;
+            const int c0 = (in ? c : c - cf) * 8, n = in ? ni : no;
+            const float *v = (in ? tz : th) + h;
+            const double *m = in ? x64 + c0 : e64 + c0;
+            const int ldm = in ? at.nip : at.nop;
+            double acc[8] = {}, b = 0.0;
+            // missing rows are zeros in all four arrays
+#pragma unroll 4
+            for (int r = 0; r < kRows; ++r) {
+                const double vr = (double)v[r * at.ld];
+                b += vr;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) acc[u] += m[r * ldm + u] * vr;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (c0 + u < n)
+                    out[in ? (size_t)(c0 + u) * nh + h : (size_t)ni * nh + nh + (size_t)h * no + c0 + u] = acc[u];
+            if (c == 0) out[(size_t)ni * nh + h] = b;
+        }
+        for (int o = tid; o <= no; o += 256) {
+            double s = 0.0;
+            if (o < no) {
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) s += e64[r * at.nop + o];
+            } else {
+#pragma unroll 8
+                for (int g = 0; g < nr * no; ++g) s += l64[g];
+            }
+            out[np - no + o] = s;
+        }
+    }
+}
+
+// Sums k_mlp_rows' entries over the blocks: 64 entries per block of 16 waves,
+// a wave adds every 16th block in order (its loads all in flight), then the
+// waves are added in order.
+__global__ void __launch_bounds__(1024) k_mlp_sum(const double *part, int tiles, int np, float *grad, double *loss) {
+    __shared__ double sh[16][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int q = blockIdx.x * 64 + lane;
+    double s = 0.0;
+    if (q <= np) {
+#pragma unroll 16
+        for (int b = wave; b < tiles; b += 16) s += part[(size_t)b * (np + 1) + q];
+    }
+    sh[wave][lane] = s;
+    __syncthreads();
+    if (wave > 0 || q > np) return;
+    s = 0.0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) s += sh[w][lane];
+    if (q < np) grad[q] = (float)s;
+    else if (loss) *loss = s;
+}
+
 __global__ void k_adam(float *p, const float *g, float *m, float *v, int n, float lr, float b1, float b2, float eps,
                        float c1, float c2) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -237,15 +426,41 @@ __global__ void k_warm_apply(const float *y, const int32_t *pos, const double *b
                              double t_min, double t_max, double *brlen) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= (int64_t)rows * no) return;
-    const int32_t at = pos[g];
-    if (at < 0) return;
-    const double v = (fmax(base[g], 0.0) + shift) * exp((double)y[g]) - shift;
-    brlen[at] = fmin(fmax(v, t_min), t_max);
+    warm_apply(WarmArgs{pos, base, shift, t_min, t_max, brlen}, g, y[g]);
 }
 
 unsigned blocks(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 
 }  // namespace
+
+bool mlp_rows_fit(int ni, int nh, int no) {
+    // (in 64 bits first: layers have up to 4096 units)
+    const int64_t np = (int64_t)ni * nh + nh + (int64_t)nh * no + no;
+    return np * 4 <= (int64_t)kMlpTileLdsMax && (int64_t)RowsLds(ni, nh, no, true).total * 4 <= (int64_t)kMlpTileLdsMax;
+}
+
+size_t mlp_rows_part_doubles(int rows, int ni, int nh, int no) {
+    return (size_t)blocks(rows, kRows) * ((size_t)ni * nh + nh + (size_t)nh * no + no + 1);
+}
+
+hipError_t mlp_rows(const float *x, const float *p, int rows, int ni, int nh, int no, float *y, const int32_t *pos,
+                    const double *base, double shift, double t_min, double t_max, double *brlen, hipStream_t s) {
+    if (rows <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_mlp_rows<false>, dim3(blocks(rows, kRows)), dim3(256),
+                       sizeof(float) * RowsLds(ni, nh, no, false).total, s, x, p, rows, ni, nh, no, y,
+                       WarmArgs{pos, base, shift, t_min, t_max, brlen}, nullptr, nullptr);
+    return hipGetLastError();
+}
+
+hipError_t mlp_rows_gradient(const float *x, const float *p, const float *target, int rows, int ni, int nh, int no,
+                             double *part, float *grad, double *loss, hipStream_t s) {
+    if (rows <= 0) return hipSuccess;
+    const int tiles = (int)blocks(rows, kRows), np = ni * nh + nh + nh * no + no;
+    hipLaunchKernelGGL(k_mlp_rows<true>, dim3(tiles), dim3(256), sizeof(float) * RowsLds(ni, nh, no, true).total, s, x,
+                       p, rows, ni, nh, no, nullptr, WarmArgs{}, target, part);
+    hipLaunchKernelGGL(k_mlp_sum, dim3(blocks(np + 1, 64)), dim3(1024), 0, s, part, tiles, np, grad, loss);
+    return hipGetLastError();
+}
 
 hipError_t mlp_forward(const float *x, const float *p, int rows, int ni, int nh, int no, float *hact, float *y,
                        hipStream_t s) {

@@ -75,7 +75,7 @@ struct ModelS {
     double Uinv[16];
     double lam[4];
     double rate[kMaxCats];
-    float WfT[16];   // W rounded to FP32 and transposed, W_im at 4 m + i (the FP32 tables of the optimisation loop)
+    alignas(16) float WfT[16];   // W rounded to FP32 and transposed, W_im at 4 m + i (the FP32 tables of the optimisation loop)
     double log_k;    // ln K
 };
 
