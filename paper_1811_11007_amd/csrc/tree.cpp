@@ -69,31 +69,35 @@ namespace {
 struct Slots {
     const Tree &t;
     std::vector<uint8_t> valid;
-    std::vector<std::vector<uint64_t>> deps;  // per slot: bitset of edges inside
-    int words;
+    // The tree hung from leaf 0: each node's parent, its place among the
+    // parent's neighbours and the parent's among its own, each edge's lower
+    // node, and per slot whether it faces the parent.
+    std::vector<int> par, in_par, to_par, low;
+    std::vector<uint8_t> faces_par;
+    std::vector<std::pair<int, uint8_t>> kept;
     std::vector<Op> *out = nullptr;
-    int updates = 0;
 
-    explicit Slots(const Tree &tree) : t(tree), valid(tree.n_slots(), 0) {
-        words = (t.n_edges + 63) / 64;
-        deps.assign(t.n_slots(), std::vector<uint64_t>(words, 0));
-        std::vector<uint8_t> done(t.n_slots(), 0);
-        std::function<void(int)> fill = [&](int s) {
-            if (done[s]) return;
-            int v = s / 3 + t.n, j = s % 3;
-            for (int q = 0; q < 3; ++q) {
-                if (q == j) continue;
-                int c = t.nbr[3 * v + q], e = t.nedge[3 * v + q];
-                deps[s][e / 64] |= 1ull << (e % 64);
-                int r = ref(c, v);
-                if (r >= 0) {
-                    fill(r);
-                    for (int w = 0; w < words; ++w) deps[s][w] |= deps[r][w];
+    explicit Slots(const Tree &tree)
+        : t(tree), valid(tree.n_slots(), 0), par(tree.n_nodes, -1), in_par(tree.n_nodes, -1),
+          to_par(tree.n_nodes, -1), low(tree.n_edges, -1), faces_par(tree.n_slots(), 0) {
+        if (t.n < 3) return;  // no slots
+        std::vector<int> todo{0};
+        while (!todo.empty()) {
+            const int v = todo.back();
+            todo.pop_back();
+            for (int q = 0; q < t.deg[v]; ++q) {
+                const int c = t.nbr[3 * v + q];
+                if (c == par[v]) {
+                    to_par[v] = q;
+                    if (v >= t.n) faces_par[(v - t.n) * 3 + q] = 1;
+                    continue;
                 }
+                par[c] = v;
+                in_par[c] = q;
+                low[t.nedge[3 * v + q]] = c;
+                todo.push_back(c);
             }
-            done[s] = 1;
-        };
-        for (int s = 0; s < t.n_slots(); ++s) fill(s);
+        }
     }
     // side of node v facing neighbour u: tip -(v+1) or slot index
     int ref(int v, int u) const {
@@ -120,12 +124,25 @@ struct Slots {
         op.a = ra; op.ea = t.nedge[3 * v + q0];
         op.b = rb; op.eb = t.nedge[3 * v + q1];
         out->push_back(op);
-        ++updates;
         valid[r] = 1;
     }
+    // The length of edge e has changed: of each internal node only the side
+    // facing e, which does not contain it, stays valid.  That is the side
+    // facing the parent, but for the nodes above e the one facing the child
+    // on the way to it.
     void touch(int e) {
-        for (int s = 0; s < t.n_slots(); ++s)
-            if (deps[s][e / 64] >> (e % 64) & 1) valid[s] = 0;
+        if (valid.empty()) return;
+        kept.clear();
+        for (int x = low[e]; par[x] >= t.n; x = par[x]) {
+            const int s = (par[x] - t.n) * 3 + in_par[x];
+            kept.push_back({s, valid[s]});
+        }
+        for (size_t s = 0; s < valid.size(); ++s) valid[s] &= faces_par[s];
+        for (const auto &k : kept) {
+            const int v = k.first / 3;
+            valid[3 * v + to_par[v + t.n]] = 0;
+            valid[k.first] = k.second;
+        }
     }
 };
 
@@ -281,16 +298,17 @@ void compile_optimize(const Tree &t, const uint8_t *mask, std::vector<Op> &first
                       std::vector<Op> &steady) {
     // depth-first edge order from the edge of leaf 0
     std::vector<int> order;
-    std::function<void(int, int)> visit = [&](int x, int y) {
+    order.reserve(t.n_edges);
+    auto visit = [&](auto &&self, int x, int y) -> void {
         for (int j = 0; j < t.deg[y]; ++j) {
             int z = t.nbr[3 * y + j];
             if (z == x) continue;
             order.push_back(t.nedge[3 * y + j]);
-            visit(y, z);
+            self(self, y, z);
         }
     };
     order.push_back(t.nedge[0]);
-    visit(0, t.nbr[0]);
+    visit(visit, 0, t.nbr[0]);
     if (t.n == 2) order.assign(1, 0);
 
     Slots s(t);
@@ -311,10 +329,10 @@ void compile_optimize(const Tree &t, const uint8_t *mask, std::vector<Op> &first
     pass(first);
     // The validity pattern after a pass is the same for every pass that
     // starts from it; iterate until the emitted program repeats.
-    std::vector<Op> prev;
     pass(steady);
+    std::vector<Op> again;
     for (int guard = 0; guard < 8; ++guard) {
-        std::vector<Op> again;
+        again.clear();
         pass(again);
         if (again.size() == steady.size() &&
             std::memcmp(again.data(), steady.data(), again.size() * sizeof(Op)) == 0)
