@@ -43,7 +43,8 @@ __device__ inline double log_prior(const double *tl, int E, double rate) {
 // passes 7.0k), 14.9k with the products on the matrix cores, the sides of two
 // steps fetched at once and the exponentials taken while they arrive (updates
 // 5.6k, row passes 6.9k); the slowest of 256 mixed trees on one block of 512
-// threads: 28.7k -> 24.6k.  Reading the ops ahead of the loop (26 scalar
+// threads: 28.7k -> 24.6k.  FP64 partials, the 48 trees: 20.9k -> 19.0k with
+// the matrix entries by row broadcasts (updates 11.7k -> 9.4k).  Reading the ops ahead of the loop (26 scalar
 // registers more) cost 5% instead.
 // FP32 with up to four categories is held to two waves per SIMD, which keeps
 // the matrix results out of the accumulation registers.
@@ -51,7 +52,7 @@ template <typename T, int BS, int KP, bool TAB_LDS, bool GRP>
 __global__ void __launch_bounds__(BS, sizeof(T) == 4 && KP <= 4 ? 2 : 1) k_optimize(const BatchArgs a, double *brlen, const OptParams opt, int ni,
                                                  int pm_lds_doubles, double *lnl_out, int32_t *passes_out,
                                                  int32_t *status_out) {
-    extern __shared__ double lds[];
+    extern __shared__ __attribute__((aligned(16))) double lds[];  // rows of 16 and 32 bytes are read whole
     __shared__ double red[2 * (BS / 64) * 3];
     __shared__ double wxs[(BS / 64) * kWx];
     __shared__ ModelS model;
@@ -156,13 +157,13 @@ __global__ void __launch_bounds__(BS, sizeof(T) == 4 && KP <= 4 ? 2 : 1) k_optim
                         if (ni == 1 && o + 1 < no) {
                             const Op nx = load_op(a.ops, o0 + o + 1);
                             if (nx.code == OP_NEWTON && (nx.a == op.dst || nx.b == op.dst)) {
-                                pre = update_and_table<T, BS, KP, kF32 ? kPmLds32 : kPmLds>(
+                                pre = update_and_table<T, BS, KP, OptPm<T, KP>::value>(
                                     v, op, nx.a == op.dst ? nx.b : nx.a, tl[nx.dst], tab, wrow, wx);
                                 have_pre = fused = true;
                             }
                         }
                     }
-                    if (!fused) do_update<T, BS, KP, kF32 ? kPmLds32 : kPmLds>(v, op, 0, ni);
+                    if (!fused) do_update<T, BS, KP, OptPm<T, KP>::value>(v, op, 0, ni);
                     if (a.prof) {
                         pc[PROF_UPDATES] += 1;
                         pc[PROF_CYC_UPDATE] += clock64() - u0;

@@ -349,10 +349,18 @@ struct Side {
 //             address space, so that the wave-uniform entries arrive by
 //             scalar loads into scalar registers instead of being broadcast
 //             to every lane;
+//   kPmLds64  FP64 copy in LDS, an entry per lane of 16 (LaneMats);
 //   kPmLds32  FP32 copy in LDS (half the broadcast bytes), for FP32 partials
 //             in the optimisation loop, whose updates then compute in FP32
 //             (update_pattern_f32).
-enum : int { kPmLds = 0, kPmConst = 1, kPmLds32 = 2 };
+enum : int { kPmLds = 0, kPmConst = 1, kPmLds32 = 2, kPmLds64 = 3 };
+
+// The optimisation loop's: with eight categories in FP64 the registers of the
+// per-lane form would spill.
+template <typename T, int KP>
+struct OptPm {
+    static constexpr int value = std::is_same<T, float>::value ? kPmLds32 : KP <= 4 ? kPmLds64 : kPmLds;
+};
 template <int PM>
 struct PmPtr {
     using type = const double *;
@@ -434,6 +442,84 @@ __device__ inline void update_pattern_f32(int K, const EdgeRows<KP> &ma, const E
     const float f = mx < thr && mx > 0.0f ? up : 1.0f;
 #pragma unroll
     for (int k = 0; k < KP; ++k) out[k] = make_float4(o[k][0] * f, o[k][1] * f, o[k][2] * f, o[k][3] * f);
+}
+
+// FP64 products in the optimisation loop: a matrix sits in one register pair,
+// entry l of 16 in lane l of every row of 16 lanes, and each fused multiply-add
+// takes its entry from there by a row broadcast, which 64-bit fused
+// multiply-adds have.  Reading the entries from LDS as broadcasts instead took
+// 64 lanes x 16 bytes per two of them: 100 such reads per update, 3k of its 8k
+// clocks on a compute unit's four waves.  A, B are the first two states summed
+// (the order of the scalar code, as in mat_vec).  Sources in lanes that the
+// execution mask switches off are not read, so every lane of a wave runs this,
+// and the block is volatile, so that it is not moved under a branch that its
+// results alone are used in.  The wait at its start covers a matrix that was
+// just moved by a vector instruction.
+#define PT_DPP(Y, L, X) "v_fmac_f64_dpp %" #Y ", %4, %" #X " row_newbcast:" #L " row_mask:0xf bank_mask:0xf\n\t"
+#define PT_DPP4(L0, L1, L2, L3, X) PT_DPP(0, L0, X) PT_DPP(1, L1, X) PT_DPP(2, L2, X) PT_DPP(3, L3, X)
+template <int A, int B>
+__device__ inline void mat_vec64(double mat, const double x[4], double y[4]) {
+    static_assert((A == 0 && B == 1) || (A == 1 && B == 0), "the first two states");
+    y[0] = y[1] = y[2] = y[3] = 0.0;
+    if constexpr (A == 1)
+        asm volatile("s_nop 1\n\t" PT_DPP4(1, 5, 9, 13, 6) PT_DPP4(0, 4, 8, 12, 5) PT_DPP4(2, 6, 10, 14, 7)
+                PT_DPP4(3, 7, 11, 15, 8)
+            : "+&v"(y[0]), "+&v"(y[1]), "+&v"(y[2]), "+&v"(y[3])
+            : "v"(mat), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]));
+    else
+        asm volatile("s_nop 1\n\t" PT_DPP4(0, 4, 8, 12, 5) PT_DPP4(1, 5, 9, 13, 6) PT_DPP4(2, 6, 10, 14, 7)
+                PT_DPP4(3, 7, 11, 15, 8)
+            : "+&v"(y[0]), "+&v"(y[1]), "+&v"(y[2]), "+&v"(y[3])
+            : "v"(mat), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]));
+}
+#undef PT_DPP4
+#undef PT_DPP
+
+// This lane's entry of every category's matrix of an edge.
+template <int KP>
+struct LaneMats {
+    double r[KP];
+    __device__ inline LaneMats(const double *pm, int e) {
+        const double *q = pm + (size_t)e * KP * 16 + (threadIdx.x & 15);
+#pragma unroll
+        for (int k = 0; k < KP; ++k) r[k] = q[k * 16];
+    }
+};
+
+// This lane's entry of W transposed.
+__device__ inline double lane_model(const ModelS *md) {
+    return md->W[(threadIdx.x & 3) * 4 + ((threadIdx.x >> 2) & 3)];
+}
+
+// update_pattern by mat_vec64 (every lane of the wave).
+template <int KP, class SA, class SB>
+__device__ inline int update_pattern_f64(int K, const LaneMats<KP> &ma, const LaneMats<KP> &mb, const SA &sa,
+                                         const SB &sb, double o[KP][4]) {
+    const double thr = 0x1p-256, up = 0x1p256;  // Store<double>::kScaleExp
+    double mx = 0.0;
+#pragma unroll
+    for (int k = 0; k < KP; ++k) {
+        double xa[4], xb[4], ya[4], yb[4];
+        sa.get(k, xa);
+        sb.get(k, xb);
+        mat_vec64<1, 0>(ma.r[k], xa, ya);
+        mat_vec64<1, 0>(mb.r[k], xb, yb);
+        const bool live = k < K;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            o[k][i] = live ? ya[i] * yb[i] : 0.0;
+            mx = fmax(mx, o[k][i]);
+        }
+    }
+    int c = sa.c + sb.c;
+    if (mx < thr && mx > 0.0) {
+#pragma unroll
+        for (int k = 0; k < KP; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[k][i] *= up;
+        c += 1;
+    }
+    return c;
 }
 
 // The steps j < ni for which this lane's wave has any of the patterns
@@ -533,6 +619,27 @@ __device__ inline void update_sides(const TreeView<T> &v, const Op &op, int base
             update_steps<BS, KP, TA, TB, kAtOnce>(v, op, ma, mb, p);
         if constexpr (kAtOnce == 2) {
             if (j < nj) update_steps<BS, KP, TA, TB, 1>(v, op, ma, mb, p);
+        }
+        return;
+    }
+    if constexpr (PM == kPmLds64) {
+        const LaneMats<KP> ma(v.pm, op.ea), mb(v.pm, op.eb);
+        const int nj = wave_steps<BS>(base, ni, v.np);
+#pragma unroll 1
+        for (int j = 0; j < nj; ++j) {
+            const int p = base + j * BS + threadIdx.x, q = min(p, v.np - 1);
+            Side<T, KP, TA> sa;
+            Side<T, KP, TB> sb;
+            sa.fetch(v, op.a, q);
+            sb.fetch(v, op.b, q);
+            double o[KP][4];
+            const int c = update_pattern_f64<KP>(v.K, ma, mb, sa, sb, o);
+            if (p < v.np) {
+#pragma unroll
+                for (int k = 0; k < KP; ++k)
+                    if (k < v.K) Store<T>::store(slot_ptr<T, KP>(v, op.dst, k, p), o[k]);
+                v.cnt[(size_t)op.dst * v.P + p] = (uint16_t)c;
+            }
         }
         return;
     }
@@ -771,6 +878,45 @@ __device__ inline void table_row(const TreeView<double> &v, const SA &sa, const 
     }
 }
 
+// The same by mat_vec64 (mat: lane_model), by every lane of the wave; lanes
+// with no pattern (valid false) fill rows that no one reads.
+template <int KP, bool FUSE, class SA, class SB>
+__device__ inline void table_row_f64(const TreeView<double> &v, double mat, const SA &sa, const SB &sb, int p,
+                                     bool valid, size_t rows, double *tab, double *wrow, double w, double logK,
+                                     const double *wxe, double &cterm, double &f1, double &f2) {
+    wrow[p] = w;
+    double L = 0.0, L1 = 0.0, L2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < KP; ++k) {
+        if (k < v.K) {
+            double xa[4], xb[4], ua[4], vb[4], sk[4];
+            sa.get(k, xa);
+            sb.get(k, xb);
+            mat_vec64<0, 1>(mat, xa, ua);
+            mat_vec64<0, 1>(mat, xb, vb);
+#pragma unroll
+            for (int m = 0; m < 4; ++m) sk[m] = ua[m] * vb[m];
+            Store<double>::store(tab + ((size_t)k * rows + p) * 4, sk);
+            if constexpr (FUSE) {
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    L += sk[m] * wxe[k * 4 + m];
+                    L1 += sk[m] * wxe[4 * kMaxCats + k * 4 + m];
+                    L2 += sk[m] * wxe[8 * kMaxCats + k * 4 + m];
+                }
+            }
+        }
+    }
+    if (!valid) return;
+    cterm += w * const_term<double>(sa.c + sb.c, logK);
+    if constexpr (FUSE) {
+        const double ia = recip(L);
+        const double r1 = L1 * ia;
+        f1 += w * r1;
+        f2 += w * (L2 * ia - r1 * r1);
+    }
+}
+
 // The same for N rows from their FP32 coefficients s (this lane's patterns
 // p0, p0 + BS, ... below np); the exponentials, read once for all N, are what
 // bounds the sums (64 lanes take 16 bytes each from LDS also when they agree).
@@ -859,6 +1005,19 @@ __device__ inline double table_sides(const TreeView<T> &v, int a, int b, int ni,
         if constexpr (kAtOnce == 2) {
             if (j < nj) table_steps<BS, KP, TA, TB, FUSE, 1>(v, a, b, p, rows, tab, wrow, row, wxe, f1, f2);
         }
+    } else if constexpr (OptPm<T, KP>::value == kPmLds64) {
+        const double mat = lane_model(v.m);
+        const int nj = wave_steps<BS>(0, ni, v.np);
+#pragma unroll 1
+        for (int j = 0; j < nj; ++j) {
+            const int p = j * BS + threadIdx.x, q = min(p, v.np - 1);
+            Side<T, KP, TA> sa;
+            Side<T, KP, TB> sb;
+            sa.fetch(v, a, q);
+            sb.fetch(v, b, q);
+            table_row_f64<KP, FUSE>(v, mat, sa, sb, p, p < v.np, rows, tab, wrow, ldg(v.w + q), logK, wxe, cterm, f1,
+                                    f2);
+        }
     } else {
 #pragma unroll 1
         for (int j = 0; j < ni; ++j) {
@@ -910,26 +1069,31 @@ __device__ inline double update_table_sides(const TreeView<T> &v, const Op &op, 
                 if (k < v.K) Store<T>::store_raw(slot_ptr<T, KP>(v, op.dst, k, p), made.r[k]);
         }
     } else {
-        // by the whole wave, which may own fewer patterns than exponentials
-        if constexpr (FUSE) wave_expo<T>(wxe, v.m, v.K, t);
-        if (p >= v.np) return 0.0;
+        static_assert(PM == kPmLds64, "the fused update and table build: FP32, or FP64 up to four categories");
+        if (wave_steps<BS>(0, 1, v.np) == 0) return 0.0;
+        const int q = min(p, v.np - 1);
         Side<T, KP, TA> sa;
         Side<T, KP, TB> sb;
         Side<T, KP, TO> so;
-        sa.fetch(v, op.a, p);
-        sb.fetch(v, op.b, p);
-        so.fetch(v, other, p);
-        const double w = ldg(v.w + p);
+        sa.fetch(v, op.a, q);
+        sb.fetch(v, op.b, q);
+        so.fetch(v, other, q);
+        const double w = ldg(v.w + q);
+        if constexpr (FUSE) wave_expo<T>(wxe, v.m, v.K, t);  // while the sides arrive
+        const LaneMats<KP> ma(v.pm, op.ea), mb(v.pm, op.eb);
         Side<T, KP, false> made;
         double o[KP][4];
-        made.c = update_pattern<T, KP, PM>(v, op, sa, sb, o);
+        made.c = update_pattern_f64<KP>(v.K, ma, mb, sa, sb, o);
 #pragma unroll
         for (int k = 0; k < KP; ++k) made.r[k] = Store<T>::pack(o[k]);
-        table_row<KP, FUSE>(v, made, so, p, (size_t)BS, tab, wrow, w, logK, wxe, cterm, f1, f2);
+        table_row_f64<KP, FUSE>(v, lane_model(v.m), made, so, p, p < v.np, (size_t)BS, tab, wrow, w, logK, wxe, cterm,
+                                f1, f2);
+        if (p < v.np) {
 #pragma unroll
-        for (int k = 0; k < KP; ++k)
-            if (k < v.K) Store<T>::store_raw(slot_ptr<T, KP>(v, op.dst, k, p), made.r[k]);
-        v.cnt[(size_t)op.dst * v.P + p] = (uint16_t)made.c;
+            for (int k = 0; k < KP; ++k)
+                if (k < v.K) Store<T>::store_raw(slot_ptr<T, KP>(v, op.dst, k, p), made.r[k]);
+            v.cnt[(size_t)op.dst * v.P + p] = (uint16_t)made.c;
+        }
     }
     return cterm;
 }
