@@ -38,14 +38,15 @@ __device__ inline double log_prior(const double *tl, int E, double rate) {
 // What bounds it: a serial chain.  An edge step is an update or two, a table,
 // one to two row passes with a block sum each, and the edge's new matrices,
 // each a few hundred instructions on one or two waves per SIMD that wait for
-// the last.  48 trees of 27 taxa on 4 blocks each, FP32 partials, clocks per
-// edge step: 16.7k when every product was scalar code (updates 7.8k, row
-// passes 7.0k), 14.9k with the products on the matrix cores, the sides of two
-// steps fetched at once and the exponentials taken while they arrive (updates
-// 5.6k, row passes 6.9k); the slowest of 256 mixed trees on one block of 512
-// threads: 28.7k -> 24.6k.  FP64 partials, the 48 trees: 20.9k -> 19.0k with
-// the matrix entries by row broadcasts (updates 11.7k -> 9.4k).  Reading the ops ahead of the loop (26 scalar
-// registers more) cost 5% instead.
+// the last.  Clocks per edge step, 48 trees of 27 taxa on 4 blocks each: FP32
+// 16.7k when every product was scalar code (updates 7.8k, row passes 7.0k),
+// 14.9k with the products on the matrix cores, the sides of two steps fetched
+// at once and the exponentials taken while they arrive, 14.5k with the sums'
+// exponentials by row broadcast (updates 5.6k, row passes 6.7k); FP64 22.1k,
+// then 19.0k with the matrix entries by row broadcast (updates 12.6k -> 9.4k)
+// and 18.2k with the exponentials.  The slowest of 256 mixed trees, one block
+// of 512 threads: 28.7k, 24.6k, 24.3k.  Reading the ops ahead of the loop (26
+// scalar registers more) cost 5% instead.
 // FP32 with up to four categories is held to two waves per SIMD, which keeps
 // the matrix results out of the accumulation registers.
 template <typename T, int BS, int KP, bool TAB_LDS, bool GRP>

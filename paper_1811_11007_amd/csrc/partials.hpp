@@ -306,6 +306,42 @@ __device__ inline void wave_expo(double *wx, const ModelS *md, int K, double t) 
     __builtin_amdgcn_wave_barrier();
 }
 
+// Up to four categories: an iteration's exponentials in registers, entry
+// k*4 + m in lane k*4 + m of every row of 16 lanes, and a pattern's sums over
+// them by row broadcast (as LDS broadcasts they were 24 reads of 8 clocks per
+// row or pair of rows).  Every lane of a wave runs these.
+struct LaneExpo {
+    double e0, e1, e2;
+    __device__ inline explicit LaneExpo(const double *wx) {
+        const int l = threadIdx.x & 15;
+        e0 = wx[l];
+        e1 = wx[4 * kMaxCats + l];
+        e2 = wx[8 * kMaxCats + l];
+    }
+};
+
+// L, L1, L2 += the four coefficients of category KAT times its exponentials,
+// in the order of m.
+#define PT_DPP(Y, E, X, L) "v_fmac_f64_dpp %" #Y ", %" #E ", %" #X " row_newbcast:%" #L " row_mask:0xf bank_mask:0xf\n\t"
+#define PT_DPP3(X, L) PT_DPP(0, 3, X, L) PT_DPP(1, 4, X, L) PT_DPP(2, 5, X, L)
+template <int KAT>
+__device__ inline void add_expo(const LaneExpo &e, const double s[4], double &L, double &L1, double &L2) {
+    asm volatile("s_nop 1\n\t" PT_DPP3(6, 10) PT_DPP3(7, 11) PT_DPP3(8, 12) PT_DPP3(9, 13)
+                 : "+&v"(L), "+&v"(L1), "+&v"(L2)
+                 : "v"(e.e0), "v"(e.e1), "v"(e.e2), "v"(s[0]), "v"(s[1]), "v"(s[2]), "v"(s[3]), "n"(KAT * 4),
+                   "n"(KAT * 4 + 1), "n"(KAT * 4 + 2), "n"(KAT * 4 + 3));
+}
+#undef PT_DPP3
+#undef PT_DPP
+
+// The same for category k < 4, known when unrolled.
+__device__ inline void add_expo(int k, const LaneExpo &e, const double s[4], double &L, double &L1, double &L2) {
+    if (k == 0) add_expo<0>(e, s, L, L1, L2);
+    else if (k == 1) add_expo<1>(e, s, L, L1, L2);
+    else if (k == 2) add_expo<2>(e, s, L, L1, L2);
+    else add_expo<3>(e, s, L, L1, L2);
+}
+
 // One side of an update or edge evaluation for one pattern: a tip code, or
 // the scaler count (CNT) and every category's partial of a slot.  TIP is a
 // template parameter so that the code fetching a pattern's sides has no
@@ -886,6 +922,7 @@ __device__ inline void table_row_f64(const TreeView<double> &v, double mat, cons
                                      const double *wxe, double &cterm, double &f1, double &f2) {
     wrow[p] = w;
     double L = 0.0, L1 = 0.0, L2 = 0.0;
+    const LaneExpo e(wxe);
 #pragma unroll
     for (int k = 0; k < KP; ++k) {
         if (k < v.K) {
@@ -897,14 +934,7 @@ __device__ inline void table_row_f64(const TreeView<double> &v, double mat, cons
 #pragma unroll
             for (int m = 0; m < 4; ++m) sk[m] = ua[m] * vb[m];
             Store<double>::store(tab + ((size_t)k * rows + p) * 4, sk);
-            if constexpr (FUSE) {
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    L += sk[m] * wxe[k * 4 + m];
-                    L1 += sk[m] * wxe[4 * kMaxCats + k * 4 + m];
-                    L2 += sk[m] * wxe[8 * kMaxCats + k * 4 + m];
-                }
-            }
+            if constexpr (FUSE) add_expo(k, e, sk, L, L1, L2);
         }
     }
     if (!valid) return;
@@ -918,29 +948,21 @@ __device__ inline void table_row_f64(const TreeView<double> &v, double mat, cons
 }
 
 // The same for N rows from their FP32 coefficients s (this lane's patterns
-// p0, p0 + BS, ... below np); the exponentials, read once for all N, are what
-// bounds the sums (64 lanes take 16 bytes each from LDS also when they agree).
+// p0, p0 + BS, ... below np).
 template <int BS, int KP, bool FUSE, int N>
 __device__ inline void table_rows(int K, int np, const float4 (&s)[N][KP], int p0, size_t rows, float *tab, double *wrow,
                                   const double (&w)[N], const double *wxe, double &f1, double &f2) {
     double L[N] = {}, L1[N] = {}, L2[N] = {};
     if constexpr (FUSE) {
+        const LaneExpo e(wxe);
 #pragma unroll
         for (int k = 0; k < KP; ++k) {
             if (k < K) {
-                double sk[N][4];
 #pragma unroll
-                for (int n = 0; n < N; ++n) Store<float>::widen(s[n][k], sk[n]);
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    const double e0 = wxe[k * 4 + m], e1 = wxe[4 * kMaxCats + k * 4 + m],
-                                 e2 = wxe[8 * kMaxCats + k * 4 + m];
-#pragma unroll
-                    for (int n = 0; n < N; ++n) {
-                        L[n] += sk[n][m] * e0;
-                        L1[n] += sk[n][m] * e1;
-                        L2[n] += sk[n][m] * e2;
-                    }
+                for (int n = 0; n < N; ++n) {
+                    double sk[4];
+                    Store<float>::widen(s[n][k], sk);
+                    add_expo(k, e, sk, L[n], L1[n], L2[n]);
                 }
             }
         }
@@ -986,7 +1008,7 @@ __device__ inline void table_steps(const TreeView<float> &v, int a, int b, int p
 // thread's rows of tab ([k][row][4]) and wrow; returns the sum of its rows'
 // t-independent lnL terms.  FUSE: also adds the rows' terms of the first
 // Newton iteration, at the exponentials wxe, to f1 and f2, from the values as
-// stored and in the order of newton_rows, so the sums are the ones a row
+// stored and in the order of the row passes, so the sums are the ones a row
 // pass over the finished table would give.
 template <typename T, int BS, int KP, bool TA, bool TB, bool FUSE, bool PAIR>
 __device__ inline double table_sides(const TreeView<T> &v, int a, int b, int ni, size_t rows, T *tab, double *wrow,
@@ -1098,14 +1120,15 @@ __device__ inline double update_table_sides(const TreeView<T> &v, const Op &op, 
     return cterm;
 }
 
-// Newton pass over N = 1 or 2 table rows r0 and r1 (r1 < 0: only r0), so that
+// Newton pass over two table rows r0 and r1 (r1 < 0: only r0), so that
 // each exponential read from the wave's LDS slice serves two patterns.  Adds
 // the rows' d1 and d2 terms, or with lnl_only their weighted log L to d0; each
 // row's sums run in the same order as for a single row.
-template <typename T, int KP, int N>
-__device__ inline void newton_rows(const T *tab, const double *wrow, size_t rows, int r0, int r1, const double *wx,
-                                   int K, bool lnl_only, double &d0, double &d1, double &d2) {
+template <typename T, int KP>
+__device__ inline void newton_rows2(const T *tab, const double *wrow, size_t rows, int r0, int r1, const double *wx,
+                                    int K, bool lnl_only, double &d0, double &d1, double &d2) {
     using Raw = typename Store<T>::Raw;
+    constexpr int N = 2;
     const bool two = r1 >= 0;
     const int r[2] = {r0, two ? r1 : r0};
     Raw raw[N][KP];
@@ -1148,6 +1171,67 @@ __device__ inline void newton_rows(const T *tab, const double *wrow, size_t rows
         const double q = L1[n] * ia;
         d1 += w[n] * q;
         d2 += w[n] * (L2[n] * ia - q * q);
+    }
+}
+
+// The same up to four categories, by every lane of a wave: rows r0 and (N = 2)
+// r0 + step, of which those below np count.
+template <typename T, int KP, int N>
+__device__ inline void newton_rows_lanes(const T *tab, const double *wrow, size_t rows, int r0, int step, int np,
+                                         const LaneExpo &e, int K, bool lnl_only, double &d0, double &d1, double &d2) {
+    typename Store<T>::Raw raw[N][KP];
+    double w[N];
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+#pragma unroll
+        for (int k = 0; k < KP; ++k)
+            if (k < K) raw[n][k] = Store<T>::load_raw(tab + ((size_t)k * rows + r0 + n * step) * 4);
+        w[n] = wrow[r0 + n * step];
+    }
+    double L[N] = {}, L1[N] = {}, L2[N] = {};
+#pragma unroll
+    for (int k = 0; k < KP; ++k) {
+        if (k < K) {
+#pragma unroll
+            for (int n = 0; n < N; ++n) {
+                double s[4];
+                Store<T>::widen(raw[n][k], s);
+                add_expo(k, e, s, L[n], L1[n], L2[n]);
+            }
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        if (r0 + n * step >= np) break;
+        if (lnl_only) {
+            d0 += w[n] * log(L[n]);
+            continue;
+        }
+        const double ia = recip(L[n]);
+        const double q = L1[n] * ia;
+        d1 += w[n] * q;
+        d2 += w[n] * (L2[n] * ia - q * q);
+    }
+}
+
+// A Newton pass over this lane's rows (nj of them, nw the most of a lane of
+// the wave) at the exponentials wx.
+template <typename T, int BS, int KP>
+__device__ inline void newton_pass(const T *tab, const double *wrow, size_t rows, int nj, int nw, int np,
+                                   const double *wx, int K, bool lnl_only, double &d0, double &d1, double &d2) {
+    if constexpr (KP <= 4) {
+        const LaneExpo e(wx);
+        int j = 0;
+#pragma unroll 1
+        for (; j + 2 <= nw; j += 2)
+            newton_rows_lanes<T, KP, 2>(tab, wrow, rows, j * BS + threadIdx.x, BS, np, e, K, lnl_only, d0, d1, d2);
+        if (j < nw)
+            newton_rows_lanes<T, KP, 1>(tab, wrow, rows, j * BS + threadIdx.x, BS, np, e, K, lnl_only, d0, d1, d2);
+    } else {
+#pragma unroll 1
+        for (int j = 0; j < nj; j += 2)
+            newton_rows2<T, KP>(tab, wrow, rows, j * BS + threadIdx.x, j + 1 < nj ? (j + 1) * BS + threadIdx.x : -1, wx,
+                                K, lnl_only, d0, d1, d2);
     }
 }
 
@@ -1283,12 +1367,7 @@ __device__ inline EdgeResult newton_edge(const TreeView<T> &v, int a, int b, dou
             // (FP32 partials: FP32 exponentials suffice for the derivatives,
             // they only steer Newton)
             wave_expo<T>(wx, v.m, v.K, t);
-#pragma unroll 1
-            for (int j = 0; j < nj; j += 2) {
-                const int r0 = j * BS + threadIdx.x;
-                if (KP > 4 || j + 1 < nw) newton_rows<T, KP, 2>(tab, wrow, rows, r0, j + 1 < nj ? r0 + BS : -1, wx, v.K, false, d0, d1, d2);
-                else newton_rows<T, KP, 1>(tab, wrow, rows, r0, -1, wx, v.K, false, d0, d1, d2);
-            }
+            newton_pass<T, BS, KP>(tab, wrow, rows, nj, nw, v.np, wx, v.K, false, d0, d1, d2);
         }
         group_sum3<BS>(d0, d1, d2, red, parity, gs);
         d1 -= opt.prior_rate;  // MAP: the exponential prior's log density is linear in t
@@ -1324,10 +1403,7 @@ __device__ inline EdgeResult newton_edge(const TreeView<T> &v, int a, int b, dou
     if (kPassLnl<T> && want_lnl) {
         wave_expo<double>(wx, v.m, v.K, t);
         double l0 = cterm, z1 = 0.0, z2 = 0.0;
-#pragma unroll 1
-        for (int j = 0; j < nj; j += 2)
-            newton_rows<T, KP, 2>(tab, wrow, rows, j * BS + threadIdx.x, j + 1 < nj ? (j + 1) * BS + threadIdx.x : -1, wx,
-                                  v.K, true, l0, z1, z2);
+        newton_pass<T, BS, KP>(tab, wrow, rows, nj, nw, v.np, wx, v.K, true, l0, z1, z2);
         group_sum3<BS>(l0, z1, z2, red, parity, gs);
         lnl = l0;
     }
