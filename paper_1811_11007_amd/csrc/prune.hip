@@ -186,21 +186,22 @@ __device__ inline void read_codes(const uint8_t *tips, int taxon, uint32_t *w) {
 
 // Scaling per pattern and category: a partial whose largest entry is below
 // 2^-256 (and not zero) is multiplied by 2^256 and the event counted.  The
-// common case is settled for all items at once on the high words (no entry is
-// negative): only when some entry of the wave is below the threshold are the
-// largest entries looked at, by folding lane masks.
+// common case is settled for all items at once on the high words, compared as
+// signed numbers: an entry below zero (a matrix has its zeros to a rounding of
+// either sign) is small, as zero is.  Only when some entry of the wave is below
+// the threshold are the largest entries looked at, by folding lane masks.
 template <int NR>
 __device__ inline void scale_partials(double *y, int *cnt) {
-    constexpr uint32_t kThr = (1023u - 256u) << 20;  // high word of 2^-256
-    uint32_t m = (uint32_t)__double2hiint(y[0]);
+    constexpr int kThr = (1023 - 256) << 20;  // high word of 2^-256
+    int m = __double2hiint(y[0]);
 #pragma unroll
-    for (int r = 1; r < NR; ++r) m = min(m, (uint32_t)__double2hiint(y[r]));
+    for (int r = 1; r < NR; ++r) m = min(m, __double2hiint(y[r]));
     if (!__any(m < kThr)) return;
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
         // bit (b, j): some entry of that category and column
-        unsigned long long big = __ballot((uint32_t)__double2hiint(y[r]) >= kThr), any = __ballot(y[r] > 0.0);
+        unsigned long long big = __ballot(__double2hiint(y[r]) >= kThr), any = __ballot(y[r] > 0.0);
         big |= big >> 32;
         big |= big >> 16;
         any |= any >> 32;
