@@ -47,7 +47,7 @@ struct Round;  // what storing a partial does to it
 
 template <>
 struct Round<float> {
-    static constexpr uint32_t kThr = (1023u - 64u) << 20;  // high word of 2^-64
+    static constexpr int kThr = (1023 - 64) << 20;  // high word of 2^-64
     static constexpr double kUp = 0x1p64;
     static constexpr int kExp = 64;
     // x to 24 bits in FP64, whatever its exponent (Veltkamp's splitting)
@@ -60,7 +60,7 @@ struct Round<float> {
 
 template <>
 struct Round<double> {
-    static constexpr uint32_t kThr = (1023u - 256u) << 20;
+    static constexpr int kThr = (1023 - 256) << 20;
     static constexpr double kUp = 0x1p256;
     static constexpr int kExp = 256;
     __device__ static inline double value(double x) { return x; }
@@ -110,14 +110,16 @@ __global__ void __launch_bounds__(kExpChunk) k_exps(const BatchArgs a, const dou
 // Scaling of a partial by the stored pass's rule: per pattern, over its
 // categories and states, when the largest entry is below 2^-S (and not zero)
 // all are multiplied by 2^S.  Returns whether any pattern of the wave was
-// scaled; cnt (null: not wanted) counts the events per item.
+// scaled; cnt (null: not wanted) counts the events per item.  High words are
+// compared as signed numbers: an entry below zero (a product has its zeros to
+// a rounding of either sign) is small, as zero is.
 template <typename T, int KP, int NI>
 __device__ __attribute__((always_inline)) inline bool scale_joint(double *y, int *cnt) {
     using L = Lanes<KP>;
     constexpr int NQ = L::NQ;
-    uint32_t m = (uint32_t)__double2hiint(y[0]);
+    int m = __double2hiint(y[0]);
 #pragma unroll
-    for (int r = 1; r < NI * NQ; ++r) m = min(m, (uint32_t)__double2hiint(y[r]));
+    for (int r = 1; r < NI * NQ; ++r) m = min(m, __double2hiint(y[r]));
     if (!__any(m < Round<T>::kThr)) return false;
     // (keeps what follows in its branch: the compiler would run it every time)
 #pragma unroll
@@ -136,7 +138,7 @@ __device__ __attribute__((always_inline)) inline bool scale_joint(double *y, int
     for (int it = 0; it < NI; ++it) {
         big[it] = 0;
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) big[it] |= __ballot((uint32_t)__double2hiint(y[it * NQ + q]) >= Round<T>::kThr);
+        for (int q = 0; q < NQ; ++q) big[it] |= __ballot(__double2hiint(y[it * NQ + q]) >= Round<T>::kThr);
         both &= big[it];
     }
     if ((~fold(both) & kCols) == 0) return false;  // one lane of each column is large enough in every item
