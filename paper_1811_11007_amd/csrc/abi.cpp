@@ -370,7 +370,7 @@ std::vector<int32_t> tiles_by_xcd(const std::vector<int> &order, const std::vect
 int reg_items(const pt_ctx *ctx, int kp, int n, int depth, int64_t patterns) {
     const int64_t want = 8LL * std::max(1, ctx->n_cu);
     int items = pt::prune_max_items(kp);
-    if (depth > 3) items /= 2;  // (more would need scratch memory)
+    if (depth > 3) items /= 2;  // (more would leave one wave per SIMD)
     while (items > 2 && (patterns / (pt::prune_tile_patterns(kp, items) / 4) < want ||
                          pt::prune_lds(kp, items, n) > ctx->lds_per_block))
         items /= 2;
@@ -1327,7 +1327,8 @@ pt_status pt_batch_loglik_noalloc(pt_ctx *ctx, pt_aln *const *alns, int32_t n_al
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return tree_E[x] > tree_E[y]; });
     // workspace layout: the sections copied from the host, then the ones the
     // kernels write; each 256-byte aligned.  A batch that only just fits takes
-    // the most items per wave, and so the fewest tiles.
+    // the most items per wave, and so the fewest tiles, also where a deep stack
+    // then leaves one wave per SIMD (no instantiation needs scratch memory).
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t o_aln = 0, o_tree = up(o_aln + sizeof(AlnDev) * B), o_ops = up(o_tree + sizeof(TreeDev) * B),
                  o_ttree = up(o_ops + sizeof(Op) * ops.size());

@@ -231,10 +231,13 @@ __device__ __attribute__((always_inline)) inline void from_slot(int slot, const 
 // result is kept in (-1: it stays the accumulator); OP_REVAL ends it.  The
 // stack is in registers, a slot chosen by wave-uniform branches; RS slots.
 // Waves per SIMD asked of the compiler, the most that need no scratch memory
-// (also two or more let it keep the products in ordinary registers).
+// (also two or more let it keep the products in ordinary registers).  A deep
+// stack of the most items takes one: only a no-allocation batch that would not
+// fit its workspace otherwise runs it, and at two it spilled 8 to 24 bytes a lane.
 template <int KP, int NI, int RS>
 constexpr int prune_waves() {
-    return RS > 3 ? 2 : NI * Lanes<KP>::NQ == 8 ? 3 : 5;
+    constexpr bool kMost = NI * Lanes<KP>::NQ == 8;
+    return RS > 3 ? (kMost ? 1 : 2) : kMost ? 3 : 5;
 }
 
 template <int KP, int NI, int RS>

@@ -64,3 +64,38 @@ def test_noalloc_matches_batch_loglik():
     got = pt.pt_batch_loglik_noalloc(ctx, A3, T3, l3.ravel(), pt.PT_FP64)
     assert np.max(np.abs(got - want) / np.abs(want)) < 1e-12
     ctx.close()
+
+
+@pytest.mark.parametrize("K,count", [(1, 6300), (2, 3500), (4, 1850), (8, 955)])
+def test_deep_trees_that_only_just_fit(K, count):
+    """32 balanced taxa (four stack slots) x 20000 patterns, so many trees that
+    they fit the workspace only with the most items per wave (about 67 MB: at
+    half as many 69 to 70 MB)."""
+    rng = np.random.default_rng(330 + K)
+    nodes, nxt, edges = list(range(32)), 32, []
+    while len(nodes) > 2:
+        up = []
+        for i in range(0, len(nodes), 2):
+            edges += [(nodes[i], nxt), (nodes[i + 1], nxt)]
+            up.append(nxt)
+            nxt += 1
+        nodes = up
+    e = np.array([(nodes[0], nodes[1])] + edges, np.int32)
+    P = 20000
+    tips = (1 << rng.integers(0, 4, size=(32, P))).astype(np.uint8)
+    w = rng.integers(1, 5, size=P).astype(np.float64)
+    rates, freqs = np.exp(rng.normal(0.0, 0.7, size=6)), rng.dirichlet(np.full(4, 8.0))
+    ctx = pt.Context(0)
+    A = [pt.Alignment(ctx, tips, w, rates, freqs, 0.6, K)]
+    T = pt.Trees([e] * count)
+    lens = rng.exponential(0.1, size=(count, len(e)))
+    got = pt.pt_batch_loglik_noalloc(ctx, A, T, lens.ravel(), pt.PT_FP64)
+    for part in (slice(0, 60), slice(count // 2, count // 2 + 60), slice(count - 60, count)):
+        want = pt.pt_batch_loglik_noalloc(ctx, A, pt.Trees([e] * 60), lens[part].ravel(), pt.PT_FP64)
+        err = np.max(np.abs(got[part] - want) / np.abs(want))
+        print("K", K, "trees", part, "max rel", err, flush=True)
+        assert err < 1e-12
+    D = oc.Data(tips, w, rates, freqs, 0.6, K)
+    for i in (0, count - 1):
+        assert abs(got[i] - oc.loglik(D, e, lens[i])) < 1e-10 * abs(got[i])
+    ctx.close()
