@@ -243,11 +243,12 @@ pt_status pt_plan_grad(pt_plan *plan, const double *d_brlen, double *d_lnl,
  * which the count has no effect.)
  * Re-tiling synchronises the device and drops the plan's captured graphs;
  * results are the same up to the order of the per-tile sums.  EINVAL for
- * another count.  pt_plan_autotune_tiles times the plan's gradient (or, with
- * no gradient, its stored likelihood pass) at each count, from the lengths
- * d_brlen, keeps the fastest for the plan and for later plans of the same
- * precision, padded categories and largest pattern and edge counts in this
- * context, and writes it to *patterns_out (NULL ok). */
+ * another count.  pt_plan_autotune_tiles times the plan's stored likelihood
+ * pass at each count, from the lengths d_brlen, keeps the fastest for the plan
+ * and for later plans of the same precision, padded categories and largest
+ * pattern and edge counts in this context, and writes it to *patterns_out
+ * (NULL ok).  A plan with a gradient and no likelihood keeps the count it has,
+ * which is what is written. */
 pt_status pt_plan_set_tile_patterns(pt_plan *plan, int32_t patterns);
 pt_status pt_plan_tile_patterns(const pt_plan *plan, int32_t *patterns);
 pt_status pt_plan_autotune_tiles(pt_plan *plan, const double *d_brlen, int32_t *patterns_out);

@@ -522,8 +522,8 @@ class Plan:
         check(lib().pt_plan_set_launch(self.h, int(block), int(groups)))
 
     def autotune_tiles(self, d_brlen):
-        """Patterns per tile of the stored pass and gradient: the fastest of
-        64, 128 and 256 on this plan (see pt.h)."""
+        """Patterns per tile of the stored pass: the fastest of 64, 128 and
+        256 on this plan (see pt.h)."""
         n = ctypes.c_int32()
         check(lib().pt_plan_autotune_tiles(self.h, ctypes.c_void_p(d_brlen.data_ptr()), ctypes.byref(n)))
         return n.value

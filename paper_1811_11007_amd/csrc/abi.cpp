@@ -1527,16 +1527,16 @@ pt_status pt_plan_autotune_tiles(pt_plan *plan, const double *d_brlen, int32_t *
         return PT_OK;
     }
     if (!d_brlen) return fail(PT_EINVAL, "d_brlen is NULL");
+    if (!(plan->kinds & PT_PLAN_LOGLIK)) {  // the gradient has tiles of its own
+        if (patterns_out) *patterns_out = plan->tile_pats;
+        return PT_OK;
+    }
     PT_HIP(hipSetDevice(plan->ctx->device));
     hipStream_t s = plan->ctx->stream;
-    // time what the tiles run: the gradient when the plan has one, else the
-    // stored likelihood pass
-    const int kind = (plan->kinds & PT_PLAN_GRAD) ? PT_PLAN_GRAD : PT_PLAN_LOGLIK;
     const int ll_prev = plan->ll_stored;
-    if (kind == PT_PLAN_LOGLIK) plan->ll_stored = 1;
-    double *d_l = nullptr, *d_g = nullptr;
+    plan->ll_stored = 1;
+    double *d_l = nullptr;
     pt_status st = dev_alloc(plan, &d_l, sizeof(double) * plan->n_trees);
-    if (!st && kind == PT_PLAN_GRAD) st = dev_alloc(plan, &d_g, sizeof(double) * std::max<int64_t>(1, plan->n_edges));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     int best = plan->tile_pats;
     float best_ms = 1e30f;
@@ -1548,7 +1548,7 @@ pt_status pt_plan_autotune_tiles(pt_plan *plan, const double *d_brlen, int32_t *
         float trial = 1e30f;
         for (int rep = 0; rep < 3 && !st; ++rep) {
             if (hipEventRecord(e0, s) != hipSuccess) { st = fail(PT_EDEVICE, "hipEventRecord failed"); break; }
-            st = enqueue(plan, kind, d_brlen, nullptr, nullptr, d_l, nullptr, nullptr, d_g, nullptr, s);
+            st = enqueue(plan, PT_PLAN_LOGLIK, d_brlen, nullptr, nullptr, d_l, nullptr, nullptr, nullptr, nullptr, s);
             if (st) break;
             float ms = 0;
             if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||

@@ -15,6 +15,7 @@ import pytest
 import torch
 
 import paper_1811_11007_amd as pt
+import synth
 from synth import workloads
 
 pytestmark = pytest.mark.gpu
@@ -175,3 +176,30 @@ def test_few_categories_at_every_tile_size(ctx):
                         assert eg < 1e-3
                 pl.close()
                 pg.close()
+
+
+def test_tuning_is_of_the_stored_pass(ctx):
+    """The gradient has tiles of its own, so a plan with nothing else keeps
+    the count it has, and no later plan starts with another."""
+    rng = np.random.default_rng(11)
+    for n in (5, 9, 14):
+        e, b = synth.yule_tree(n, rng, mean=0.1)
+        tips = (1 << rng.integers(0, 4, size=(n, 700 + n))).astype(np.uint8)
+        A = pt.Alignment(ctx, tips, np.ones(700 + n), np.ones(6), np.full(4, 0.25), 0.5, 4)
+        d = torch.tensor(b, dtype=torch.float64, device="cuda:0")
+        for prec in (pt.PT_FP64, pt.PT_FP32):
+            plan = pt.Plan(ctx, [A], pt.Trees([e]), pt.PT_PLAN_GRAD, prec)
+            for pats in (64, 128):
+                plan.set_tile_patterns(pats)
+                assert plan.autotune_tiles(d) == pats and plan.tile_patterns() == pats
+            plan.close()
+            plan = pt.Plan(ctx, [A], pt.Trees([e]), pt.PT_PLAN_LOGLIK, prec)
+            assert plan.tile_patterns() == 256
+            plan.close()
+        # with a likelihood beside it, the stored pass is what is timed
+        plan = pt.Plan(ctx, [A], pt.Trees([e]), pt.PT_PLAN_GRAD | pt.PT_PLAN_LOGLIK, pt.PT_FP64)
+        best = plan.autotune_tiles(d)
+        plan.close()
+        plan = pt.Plan(ctx, [A], pt.Trees([e]), pt.PT_PLAN_LOGLIK, pt.PT_FP64)
+        assert best in (64, 128, 256) and plan.tile_patterns() == best
+        plan.close()
