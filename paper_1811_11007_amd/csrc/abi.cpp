@@ -1938,6 +1938,7 @@ struct pt_mlp {
 namespace {
 
 void mlp_free_scratch(pt_mlp *m) {
+    if ((void *)m->d_h == (void *)m->d_part) m->d_h = nullptr;
     for (void *p : {(void *)m->d_h, (void *)m->d_y, (void *)m->d_dy, (void *)m->d_dz, (void *)m->d_rl,
                     (void *)m->d_part})
         if (p) (void)hipFree(p);
@@ -1946,18 +1947,20 @@ void mlp_free_scratch(pt_mlp *m) {
     m->cap = 0;
 }
 
-// What a pass needs in memory: of a network that fits in LDS, the blocks' sums
-// of a gradient (and the activations, where outputs overlap the inputs and
-// the layers run one after the other).
+// What a pass needs in memory.  Of a network that fits in LDS that is the
+// blocks' sums of a gradient; where outputs overlap the inputs and the layers
+// run one after the other, the activations take the same memory (an array of
+// their own was a second allocation that a gradient never read).
 pt_status mlp_scratch(pt_mlp *m, int rows) {
     if (rows <= m->cap) return PT_OK;
     mlp_free_scratch(m);
-    const size_t r = (size_t)rows;
-    PT_HIP(hipMalloc(&m->d_h, sizeof(float) * r * m->nh));
+    const size_t r = (size_t)rows, h = sizeof(float) * r * m->nh;
     if (pt::mlp_rows_fit(m->ni, m->nh, m->no)) {
-        PT_HIP(hipMalloc(&m->d_part, sizeof(double) * pt::mlp_rows_part_doubles(rows, m->ni, m->nh, m->no)));
+        PT_HIP(hipMalloc(&m->d_part, std::max(h, sizeof(double) * pt::mlp_rows_part_doubles(rows, m->ni, m->nh, m->no))));
+        m->d_h = reinterpret_cast<float *>(m->d_part);
     } else {
-        PT_HIP(hipMalloc(&m->d_dz, sizeof(float) * r * m->nh));
+        PT_HIP(hipMalloc(&m->d_h, h));
+        PT_HIP(hipMalloc(&m->d_dz, h));
         PT_HIP(hipMalloc(&m->d_y, sizeof(float) * r * m->no));
         PT_HIP(hipMalloc(&m->d_dy, sizeof(float) * r * m->no));
         PT_HIP(hipMalloc(&m->d_rl, sizeof(double) * r));

@@ -66,3 +66,22 @@ def test_outputs_over_inputs(ctx):
     torch.cuda.synchronize()
     assert np.array_equal(X.cpu().numpy(), want)
     net.close()
+
+
+def test_scratch_of_a_network_that_fits(ctx):
+    """A gradient of a network that fits in LDS takes memory for its blocks'
+    sums and none for activations (128 MiB here)."""
+    ni, nh, no, rows = 14, 128, 5, 1 << 18
+    net, p, x, t = network(ctx, ni, nh, no, 1)
+    X = torch.zeros(rows, ni, dtype=torch.float32, device="cuda:0")
+    T = torch.zeros(rows, no, dtype=torch.float32, device="cuda:0")
+    g = torch.zeros(net.n_params, dtype=torch.float32, device="cuda:0")
+    net.gradient(X[:16], T[:16], g)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    net.gradient(X, T, g)
+    torch.cuda.synchronize()
+    taken, sums = free - torch.cuda.mem_get_info()[0], 8 * (rows // 16) * (net.n_params + 1)
+    print("taken", taken, "sums", sums, flush=True)
+    assert taken <= sums + (32 << 20)
+    net.close()
