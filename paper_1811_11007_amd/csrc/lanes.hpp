@@ -88,6 +88,18 @@ __device__ inline Op load_op(const Op *ops, int64_t i) {
     return op;
 }
 
+// A tree's descriptor, the same way.
+__device__ inline TreeDev load_tree(const TreeDev *trees, int b) {
+    static_assert(sizeof(TreeDev) % sizeof(int32_t) == 0, "whole words");
+    const __attribute__((address_space(4))) int32_t *q = (const __attribute__((address_space(4))) int32_t *)(trees + b);
+    int32_t w[sizeof(TreeDev) / sizeof(int32_t)];
+#pragma unroll
+    for (size_t i = 0; i < sizeof(TreeDev) / sizeof(int32_t); ++i) w[i] = q[i];
+    TreeDev td;
+    __builtin_memcpy(&td, w, sizeof(td));
+    return td;
+}
+
 // Moves a double across lanes with a DPP row shift; lanes whose source lies
 // outside their row of 16 receive 0.
 template <int CTRL>

@@ -84,11 +84,17 @@ __global__ void __launch_bounds__(BS, sizeof(T) == 4 && KP <= 4 ? 2 : 1) k_optim
         } else {
             if (tid == 0) q_sh = atomicAdd(a.queue, 1);
             __syncthreads();
-            q = q_sh;
+            q = __builtin_amdgcn_readfirstlane(q_sh);
             if (q >= a.n_trees) break;
         }
-        const int b = a.order[q];
-        const TreeDev td = a.trees[b];
+        // The tree's descriptor is wave-uniform and no launch writes it: scalar
+        // loads.  (In vector registers it was also a hazard: with eight
+        // categories in FP64 the compiler copied td.edge_off to accumulation
+        // registers at the end of a divergent loop, before the instruction that
+        // restores the execution mask, so that no lane was copied, and the
+        // final lengths went to an address of leftover values.)
+        const int b = ((const __attribute__((address_space(4))) int32_t *)a.order)[q];
+        const TreeDev td = load_tree(a.trees, b);
         const AlnDev *aln = a.alns + td.aln;
         const int E = td.n_edges;
         // FP64 partials: the matrices, then the lengths, in LDS.  FP32

@@ -89,3 +89,32 @@ def test_edges_of_steps(ctx, columns, P, K):
         assert np.all(np.abs(t32 - t64) <= STEP_REL * (t64 + start))
     for plan in plans.values():
         plan.close()
+
+
+@pytest.mark.parametrize("K", [1, 4, 5, 8])
+@pytest.mark.parametrize("prec", [pt.PT_FP64, pt.PT_FP32])
+def test_lengths_of_a_batch_at_their_place(ctx, columns, K, prec):
+    """One block per tree: every tree of a batch has the lengths that it has
+    alone, bit for bit, and nothing else is written."""
+    e, b, tips = columns
+    rng = np.random.default_rng(95)
+    A = pt.Alignment(ctx, np.ascontiguousarray(tips[:, :200]), np.ones(200), RATES, FREQS, 0.6, K)
+    start = rng.exponential(0.1, size=(7, len(b)))
+
+    def run(lens):
+        plan = pt.Plan(ctx, [A], pt.Trees([e] * len(lens)), pt.PT_PLAN_OPTIMIZE, prec)
+        plan.set_launch(256, 1)
+        d = torch.full((lens.size + 64,), 7.0, dtype=torch.float64, device="cuda:0")
+        d[:lens.size] = torch.tensor(lens.ravel())
+        lnl = torch.zeros(len(lens), dtype=torch.float64, device="cuda:0")
+        plan.optimize(d, lnl)
+        torch.cuda.synchronize()
+        plan.close()
+        out = d.cpu().numpy()
+        assert np.all(out[lens.size:] == 7.0)
+        return out[:lens.size].reshape(lens.shape)
+
+    got = run(start)
+    assert np.all(np.any(got != start, axis=1))
+    for t in range(len(start)):
+        assert np.array_equal(run(start[t:t + 1])[0], got[t]), t
