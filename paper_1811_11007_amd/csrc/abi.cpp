@@ -396,12 +396,7 @@ pt_status configure_shape(pt_plan *pl, int block, int groups = 1) {
     const size_t esz = store_bytes(pl->precision);
     const size_t tab_lds = (size_t)block * ni * pl->kp * 4 * esz + (size_t)block * ni * 8;
     const size_t pm_bytes = (size_t)pl->pm_doubles * 8;
-    // Eight categories in FP64 with more than one pattern per thread: a launch
-    // of 257 patterns with the table in LDS (148 KB per block) ended in a
-    // memory aperture violation whose cause is not known, so there the table
-    // lives in memory, with the same sums.
-    const bool lds_off = pl->precision == PT_FP64 && pl->kp == 8 && ni > 1;
-    const bool lds_ok = !lds_off && pm_bytes + tab_lds + kOptStaticLds <= pl->ctx->lds_per_block;
+    const bool lds_ok = pm_bytes + tab_lds + kOptStaticLds <= pl->ctx->lds_per_block;
     if (pt::optimize_spill_bytes(pl->precision, block, pl->kp, lds_ok, grouped) != 0)
         return fail(PT_EUNSUPPORTED, "optimisation kernel shape needs register spills");
     const size_t lds = pm_bytes + (lds_ok ? tab_lds : 0);

@@ -47,9 +47,6 @@ def columns():
 @pytest.mark.parametrize("K", [1, 2, 4, 5])
 @pytest.mark.parametrize("P", [1, 63, 65, 129, 255, 257, 511, 513, 769, 1025, 1100])
 def test_edges_of_steps(ctx, columns, P, K):
-    if K == 5 and P > 256:
-        pytest.skip("eight padded categories in FP64 with two patterns per thread and the table in LDS faulted the GPU; "
-                    "that path is switched off, its cause not known")
     e, b, tips = columns
     tips = np.ascontiguousarray(tips[:, :P])
     w = np.random.default_rng(P).integers(1, 5, size=P).astype(np.float64)

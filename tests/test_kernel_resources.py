@@ -65,7 +65,7 @@ def copies_before_joins(listing):
             if re.match(r"s_c?branch", m.group(1)):
                 to = re.search(r"<([^+>]+)(?:\+0x([0-9a-f]+))?>", line)
                 targets.add(base[to.group(1)] + int(to.group(2) or "0", 16))
-    copy = re.compile(r"v_accvgpr_(read|write)|v_mov_b(32|64)\S* [va][\d\[:\]]+, [va][\d\[]")
+    copy = re.compile(r"v_accvgpr_(read|write|mov)|v_mov_b(32|64)\S* [va][\d\[:\]]+, [va][\d\[]")
     found = []
     for i, (kernel, addr, _) in enumerate(code):
         if addr not in targets and not (i and re.match(r"s_c?branch", code[i - 1][2])):
