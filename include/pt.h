@@ -481,7 +481,8 @@ pt_status pt_mlp_gradient(pt_mlp *mlp, const float *d_x, const float *d_target, 
  * i.e. the outputs are log-ratios of shifted lengths of a neighbour and its
  * parent (shift > 0 keeps lengths near zero from dominating).  d_pos: device
  * int32[rows][n_out], indices into d_brlen (distinct and in range: the
- * caller's responsibility); d_base: device double[rows][n_out]. */
+ * caller's responsibility); d_base: device double[rows][n_out].  d_brlen may
+ * start within d_x, but not run into it from before. */
 pt_status pt_mlp_warm_start(pt_mlp *mlp, const float *d_x, int32_t rows, const int32_t *d_pos, const double *d_base,
                             double shift, double t_min, double t_max, double *d_brlen, void *stream);
 /* One Adam step on that loss. */

@@ -1933,7 +1933,7 @@ struct pt_mlp {
 namespace {
 
 void mlp_free_scratch(pt_mlp *m) {
-    if ((void *)m->d_h == (void *)m->d_part) m->d_h = nullptr;
+    if ((void *)m->d_h == (void *)m->d_part) m->d_h = m->d_y = nullptr;
     for (void *p : {(void *)m->d_h, (void *)m->d_y, (void *)m->d_dy, (void *)m->d_dz, (void *)m->d_rl,
                     (void *)m->d_part})
         if (p) (void)hipFree(p);
@@ -1944,15 +1944,17 @@ void mlp_free_scratch(pt_mlp *m) {
 
 // What a pass needs in memory.  Of a network that fits in LDS that is the
 // blocks' sums of a gradient; where outputs overlap the inputs and the layers
-// run one after the other, the activations take the same memory (an array of
-// their own was a second allocation that a gradient never read).
+// run one after the other, activations and predictions take the same memory
+// (arrays of their own were an allocation that a gradient never read).
 pt_status mlp_scratch(pt_mlp *m, int rows) {
     if (rows <= m->cap) return PT_OK;
     mlp_free_scratch(m);
     const size_t r = (size_t)rows, h = sizeof(float) * r * m->nh;
     if (pt::mlp_rows_fit(m->ni, m->nh, m->no)) {
-        PT_HIP(hipMalloc(&m->d_part, std::max(h, sizeof(double) * pt::mlp_rows_part_doubles(rows, m->ni, m->nh, m->no))));
+        const size_t sums = sizeof(double) * pt::mlp_rows_part_doubles(rows, m->ni, m->nh, m->no);
+        PT_HIP(hipMalloc(&m->d_part, std::max(h + sizeof(float) * r * m->no, sums)));
         m->d_h = reinterpret_cast<float *>(m->d_part);
+        m->d_y = m->d_h + r * m->nh;
     } else {
         PT_HIP(hipMalloc(&m->d_h, h));
         PT_HIP(hipMalloc(&m->d_dz, h));
@@ -2045,7 +2047,10 @@ pt_status pt_mlp_warm_start(pt_mlp *mlp, const float *d_x, int32_t rows, const i
     if (!(t_min > 0.0) || !(t_max > t_min)) return fail(PT_EINVAL, "need 0 < t_min < t_max");
     if (!(shift > 0.0) || !std::isfinite(shift)) return fail(PT_EINVAL, "need shift > 0");
     hipStream_t s = (hipStream_t)stream;
-    if (pt::mlp_rows_fit(mlp->ni, mlp->nh, mlp->no)) {
+    // lengths written over the inputs: every row's outputs first, as in
+    // pt_mlp_forward (how far the lengths go is not known here)
+    if (pt::mlp_rows_fit(mlp->ni, mlp->nh, mlp->no) &&
+        !overlap(d_x, sizeof(float) * (size_t)rows * mlp->ni, d_brlen, sizeof(double))) {
         PT_HIP(pt::mlp_rows(d_x, mlp->d_p, rows, mlp->ni, mlp->nh, mlp->no, nullptr, d_pos, d_base, shift, t_min, t_max,
                             d_brlen, s));
         return PT_OK;

@@ -68,6 +68,31 @@ def test_outputs_over_inputs(ctx):
     net.close()
 
 
+@pytest.mark.parametrize("rows", [100, 60000])
+def test_start_lengths_over_inputs(ctx, rows):
+    """Start lengths may be written over the inputs they are made from, by more
+    blocks than the device runs at once too."""
+    ni, nh, no = 14, 128, 5
+    net, p, x, t = network(ctx, ni, nh, no, rows)
+    base = torch.rand(rows, no, dtype=torch.float64, device="cuda:0")
+    pos = torch.randperm(rows * no, dtype=torch.int32, device="cuda:0")
+    X = torch.tensor(x, device="cuda:0")
+    call = pt._lib.lib().pt_mlp_warm_start
+
+    def run(X, brlen):
+        pt._lib.check(call(net.h, X.data_ptr(), rows, pos.data_ptr(), base.data_ptr(), 0.01, 1e-8, 100.0,
+                           brlen.data_ptr(), None))
+        torch.cuda.synchronize()
+        return brlen.cpu().numpy()
+
+    want = run(X, torch.zeros(rows * no, dtype=torch.float64, device="cuda:0"))
+    for first in (0, rows):  # doubles from the inputs' start
+        Y = X.clone()
+        got = run(Y, Y.view(-1).view(torch.float64)[first:first + rows * no])
+        assert np.array_equal(got, want), first
+    net.close()
+
+
 def test_scratch_of_a_network_that_fits(ctx):
     """A gradient of a network that fits in LDS takes memory for its blocks'
     sums and none for activations (128 MiB here)."""
