@@ -324,7 +324,7 @@ def main():
             return ms, by, l.cpu().numpy()
 
         # the stored post-order pass (every partial written to and read from
-        # HBM, as in an optimisation's first pass or a gradient's lower half)
+        # HBM, as in an optimisation's first pass)
         ms3, by3, l3 = time_loglik(pt.PT_FP32, pt.PT_LOGLIK_STORED)
         ms3d, by3d, l3d = time_loglik(pt.PT_FP64, pt.PT_LOGLIK_STORED)
         # the register-resident pass (no partial stored)
@@ -407,8 +407,7 @@ def main():
         out["gradient"]["all_within_1e-3"] = e4 < 1e-3
         plan4.close()
         out["pruning"] = {"workload": "512 topologies over 27x1949, 36x1812, 50x1133, 64x1008 GTR+G4, FP32 "
-                                      "partials stored in HBM (the post-order pass that starts an optimisation "
-                                      "or a gradient)",
+                                      "partials stored in HBM (the post-order pass that starts an optimisation)",
                           "ms_per_call": round(ms3, 4), "algorithmic_bytes": by3,
                           "achieved_GBs": round(by3 / (ms3 / 1e3) / 1e9, 1),
                           "frac_of_peak": round(by3 / (ms3 / 1e3) / 1e9 / HBM_PEAK_GBS, 4),
@@ -426,7 +425,7 @@ def main():
         d3r = np.abs(l3r - start3)
         out["loglik_registers"] = {
             "workload": "lnL of the same 512 topologies with no partial stored (FP64 partials of each "
-                        "pattern and category in registers and an LDS stack)",
+                        "pattern and category in registers)",
             "ms_per_call": round(ms3r, 4), "trees_per_s": round(T3.n_trees / (ms3r / 1e3), 1),
             "speedup_over_stored_fp32": round(ms3 / ms3r, 2),
             "max_abs_dlnl_vs_oracle": float(d3r.max()), "all_within_1e-4": bool(np.all(d3r <= 1e-4)),

@@ -78,7 +78,7 @@ struct pt_ctx {
     // tuned (threads per block, blocks per tree) of the optimisation kernel,
     // per (precision, padded categories, largest pattern count)
     std::map<std::tuple<int, int, int>, std::pair<int, int>> tuned;
-    // tuned patterns per tile of the stored pass and gradient, per
+    // tuned patterns per tile of the stored pass, per
     // (precision, padded categories, largest pattern count, largest edge count)
     std::map<std::tuple<int, int, int, int>, int> tuned_tiles;
     // device memory of destroyed plans: a search creates a plan of the same
@@ -906,7 +906,7 @@ pt_status enqueue(pt_plan *pl, int kind, const double *brlen_c, double *brlen, c
         // lnL with every partial in FP64 registers: the likelihood call
         // itself, and the lnL a gradient call with FP32 partials reports
         // (FP32 storage puts ~1e-4 of rounding noise into lnL at a few
-        // thousand sites; the gradient keeps its stored partials)
+        // thousand sites; the derivatives keep their rounded partials)
         if (reg_ll || (g && pl->reg_ok && pl->precision == PT_FP32)) {
             pt::BatchArgs r = reg_args(pl);
             if ((e = pt::launch_pmat_lanes(r, brlen_c, pl->max_E, s)) != hipSuccess) goto bad;

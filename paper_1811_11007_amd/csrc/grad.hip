@@ -167,7 +167,7 @@ __device__ __attribute__((always_inline)) inline bool scale_joint(double *y, int
     return scaled;
 }
 
-// Programs come from compile_grad_lanes.  Each side reference is a leaf's
+// Programs come from compile_grad.  Each side reference is a leaf's
 // tip (>= 0), the accumulator (REF_ACC) or the partial in slot REF_STACK0 - ref:
 //   OP_GUP    acc = b of the node over sides a (edge ea) and b (edge eb), also
 //             stored in slot dst;
