@@ -201,7 +201,7 @@ __device__ inline void scale_partials(double *y, int *cnt) {
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
         // bit (b, j): some entry of that category and column
-        unsigned long long big = __ballot(__double2hiint(y[r]) >= kThr), any = __ballot(y[r] > 0.0);
+        unsigned long long big = __ballot(y[r] >= 0x1p-256), any = __ballot(y[r] > 0.0);
         big |= big >> 32;
         big |= big >> 16;
         any |= any >> 32;
