@@ -42,10 +42,11 @@ __device__ inline double log_prior(const double *tl, int E, double rate) {
 // 16.7k when every product was scalar code (updates 7.8k, row passes 7.0k),
 // 14.9k with the products on the matrix cores, the sides of two steps fetched
 // at once and the exponentials taken while they arrive, 14.5k with the sums'
-// exponentials by row broadcast (updates 5.6k, row passes 6.7k); FP64 22.1k,
-// then 19.0k with the matrix entries by row broadcast (updates 12.6k -> 9.4k)
-// and 18.2k with the exponentials.  The slowest of 256 mixed trees, one block
-// of 512 threads: 28.7k, 24.6k, 24.3k.  Reading the ops ahead of the loop (26
+// exponentials by row broadcast, 14.2k with the tree's descriptor in scalar
+// registers (updates 5.4k, row passes 6.8k); FP64 22.1k, then 19.0k with the
+// matrix entries by row broadcast (updates 12.6k -> 9.4k), 18.2k with the
+// exponentials and 18.1k now.  The slowest of 256 mixed trees, one block of 512
+// threads: 28.7k, 24.6k, 24.3k, 24.0k.  Reading the ops ahead of the loop (26
 // scalar registers more) cost 5% instead.
 // FP32 with up to four categories is held to two waves per SIMD, which keeps
 // the matrix results out of the accumulation registers.
