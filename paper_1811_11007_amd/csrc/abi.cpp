@@ -754,7 +754,8 @@ pt_status plan_build(pt_ctx *ctx, pt_aln *const *alns, int32_t n_alns, const pt_
     int64_t need = clv_off * (int64_t)store_bytes(precision) + cnt_off * 2 + pm_off * 8 +
                    n_ops * (int64_t)sizeof(Op) + (int64_t)tiles * 12 +
                    (int64_t)pt::grad_part_doubles(pl->n_tiles_gr, pl->max_E) * 8 + (int64_t)pl->n_tiles_gr * 4 +
-                   (int64_t)NE * 16 + (int64_t)B * 4 * sizeof(TreeDev) + (int64_t)pl->n_tiles_reg * 28;
+                   (int64_t)NE * 16 + (int64_t)B * 4 * sizeof(TreeDev) +
+                   (int64_t)pl->n_tiles_reg * 16;  // a tile's tree, number and sum
     int64_t cap = arena_cap();
     if (cap > 0 && need > cap)
         return fail(PT_ENOMEM, "batch needs " + std::to_string(need) + " device bytes, over PT_ARENA_CAP_BYTES");

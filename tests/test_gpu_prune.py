@@ -154,3 +154,15 @@ def test_optimised_lnl_of_the_deepest_tree(ctx):
     assert status[0] == 0 and np.all(out[mask == 0] == b[mask == 0]) and np.any(out != b)
     want = oc.loglik(oc.Data(tips, np.ones(P), np.ones(6), np.full(4, 0.25), 1.0, 1), e, out)
     close(lnl, np.array([want]), "1024 taxa, lnL %.2f" % want, 1e-11)
+
+
+def test_two_taxa_under_an_arena_cap(ctx, monkeypatch):
+    """Trees of two taxa have no partials, so what a plan of them needs is their
+    tiles' words: 16000 patterns in four categories keep within 12000 bytes."""
+    rng = np.random.default_rng(710)
+    e, b, tips, w = problem(2, 16000, 4, rng, True)
+    A = pt.Alignment(ctx, tips, w, RATES, FREQS, 0.6, 4)
+    want = pt.pt_batch_loglik(ctx, [A], pt.Trees([e]), b)
+    monkeypatch.setenv("PT_ARENA_CAP_BYTES", "12000")
+    assert np.array_equal(pt.pt_batch_loglik(ctx, [A], pt.Trees([e]), b), want)
+    close(want, np.array([oc.loglik(oc.Data(tips, w, RATES, FREQS, 0.6, 4), e, b)]), "two taxa", 1e-11)
