@@ -291,7 +291,8 @@ pt_status check_lengths(const double *brlen, int64_t n) {
 
 size_t store_bytes(int precision) { return precision == PT_FP32 ? 4 : 8; }
 
-// Device bytes a one-tree plan of this shape needs (for the arena cap).
+// Device bytes a one-tree plan of this shape is taken to need: a tree for which
+// they exceed the arena cap is refused.
 int64_t tree_bytes(int n, const AlnDev &a, int precision, int kinds) {
     const int E = n == 2 ? 1 : 2 * n - 3, slots = n >= 3 ? 3 * (n - 2) : 0;
     const int64_t items = (int64_t)a.P * a.Kp;
@@ -303,6 +304,29 @@ int64_t tree_bytes(int n, const AlnDev &a, int precision, int kinds) {
     }
     return b;
 }
+
+// What plan_build counts of a chunk's trees towards the arena cap, kept while
+// trees are added.
+struct ChunkBytes {
+    int64_t trees = 0, grad_tiles = 0;
+    int max_E = 1;
+    void add(int n, const AlnDev &a, int precision, int kind) {
+        const int64_t E = n == 2 ? 1 : 2 * n - 3, slots = n - 2, opt = kind == PT_PLAN_OPTIMIZE ? 4 : 1;
+        const int64_t slot = (int64_t)a.P * a.Kp * 4 * store_bytes(precision);
+        trees += kind == PT_PLAN_GRAD ? slots * slot : 3 * slots * (slot + 2 * a.P);
+        // matrices, programs (an optimisation's: up to four ops per edge and
+        // pass), lengths, descriptors
+        trees += E * a.Kp * 128 + opt * 64 * (E + 1) + E * 16 + 4 * (int64_t)sizeof(TreeDev) + 256;
+        trees += (a.P + 31) / 32 * 16 + (a.P + 63) / 64 * 12;  // likelihood tiles, the smallest
+        if (kind == PT_PLAN_GRAD) {
+            const int pats = pt::grad_tile_patterns(a.Kp);
+            grad_tiles += (a.P + pats - 1) / pats;
+            max_E = std::max(max_E, (int)E);
+        }
+    }
+    // (a gradient tile has a row of the longest tree's sums)
+    int64_t total() const { return trees + 8 * (int64_t)pt::grad_part_doubles((int)grad_tiles, max_E) + 4 * grad_tiles; }
+};
 
 // Static LDS of the optimisation kernel at 512 threads (reduction buffers,
 // per-wave exponential tables, model, counter), rounded up.
@@ -985,19 +1009,22 @@ pt_status make_chunks(pt_aln *const *alns, const pt_trees *trees, const std::vec
     const int B = trees->n_trees;
     for (int kp : {1, 2, 4, 8}) {
         std::vector<int> cur;
-        int64_t used = 0;
+        ChunkBytes used;
         for (int b = 0; b < B; ++b) {
             const AlnDev &ad = alns[trees->aln_index[b]]->desc;
             if (ad.Kp != kp) continue;
             if (cap > 0) {
-                int64_t need = tree_bytes(ntx[b], ad, precision, kinds) + 4096;
-                if (need > cap) return fail(PT_ENOMEM, "tree " + std::to_string(b) + " alone exceeds PT_ARENA_CAP_BYTES");
-                if (used + need > cap && !cur.empty()) {
+                if (tree_bytes(ntx[b], ad, precision, kinds) + 4096 > cap)
+                    return fail(PT_ENOMEM, "tree " + std::to_string(b) + " alone exceeds PT_ARENA_CAP_BYTES");
+                ChunkBytes with = used;
+                with.add(ntx[b], ad, precision, kinds);
+                if (with.total() > cap && !cur.empty()) {
                     out.push_back(cur);
                     cur.clear();
-                    used = 0;
+                    with = ChunkBytes();
+                    with.add(ntx[b], ad, precision, kinds);
                 }
-                used += need;
+                used = with;
             }
             cur.push_back(b);
         }

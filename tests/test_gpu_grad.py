@@ -87,3 +87,28 @@ def test_batch_over_alignments(ctx):
             assert abs(lnl[t] - wl) <= 1e-9 * abs(wl)
             assert np.all(np.abs(g[s] - wg) <= tol * np.maximum(1.0, np.abs(wg)))
             assert np.all(np.abs(h[s] - wh) <= tol * np.maximum(1.0, np.abs(wh)))
+
+
+@pytest.mark.parametrize("prec", [pt.PT_FP64, pt.PT_FP32])
+def test_small_trees_under_an_arena_cap(ctx, monkeypatch, prec):
+    """Batches are split so that every part keeps within the cap, also where a
+    plan is mostly its tiles' rows of sums: trees of two taxa, and of three
+    beside one of forty."""
+    rng = np.random.default_rng(880)
+    alns, tops, lens, idx = [], [], [], []
+    for i, (n, P, count) in enumerate(((2, 16000, 30), (3, 4000, 30), (40, 64, 1))):
+        tips = (1 << rng.integers(0, 4, size=(n, P))).astype(np.uint8)
+        alns.append(pt.Alignment(ctx, tips, np.ones(P), RATES, FREQS, 0.6, 4))
+        for _ in range(count):
+            e, b = synth.yule_tree(n, rng, mean=0.1)
+            tops.append(e)
+            lens.append(b + 0.01)
+            idx.append(i)
+    order = rng.permutation(len(tops))
+    T = pt.Trees([tops[i] for i in order], [idx[i] for i in order])
+    b = np.concatenate([lens[i] for i in order])
+    want = pt.pt_batch_branch_grad(ctx, alns, T, b, prec, hess=True)
+    monkeypatch.setenv("PT_ARENA_CAP_BYTES", str(4 << 20))
+    got = pt.pt_batch_branch_grad(ctx, alns, T, b, prec, hess=True)
+    for g, x in zip(got, want):
+        assert np.allclose(g, x, rtol=1e-12, atol=0)
